@@ -293,3 +293,38 @@ def test_gemm_batched_tile_shapes(variant):
     for o, b0, r, bd in zip(out, base, ref, bnd):
         assert np.all(np.abs(o.cpu().numpy() - r) <= bd + 1e-300)
         assert torch.equal(o, b0)
+
+
+@pytest.mark.parametrize("K", [15, 511, 512, 513, 1041])
+def test_gemm_batched_long_inner_dimensions(K):
+    """Inner dimensions around the kernel's chunks of 512 k and its slices of
+    16, with leading dimensions beyond the rows and NaN just past every row
+    and column that belongs to the product: within 2 gamma_K |A||B| of the
+    host's product, and the same bits in every tile shape and in the shape the
+    library picks by itself."""
+    g = np.random.default_rng(K)
+    As, Bs, Cs, tr, ref, bnd = [], [], [], [], [], []
+    for M, N, t in [(33, 17, 0), (70, 65, 1), (1, 1, 0), (130, 5, 1)]:
+        A = g.standard_normal((K, M) if t else (M, K))
+        B, C = g.standard_normal((K, N)), g.standard_normal((M, N))
+        opA = A.T if t else A
+        ref.append(opA @ B - C)
+        bnd.append(2 * _gamma(K) * (np.abs(opA) @ np.abs(B)) + 4 * U * (np.abs(opA @ B) + np.abs(C)))
+        pads = [np.full((x.shape[0] + 1, x.shape[1] + 3), np.nan) for x in (A, B, C)]
+        views = []
+        for pad, x in zip(pads, (A, B, C)):
+            pad[:-1, :-3] = x
+            views.append(torch.from_numpy(pad).cuda()[:-1, :-3])
+        As.append(views[0])
+        Bs.append(views[1])
+        Cs.append(views[2])
+        tr.append(bool(t))
+    print(f"gemm_batched K={K}", flush=True)
+    first = None
+    for v in range(-1, P.hss_gemm_variants()):
+        out = P.hss_gemm_batched(As, Bs, [c.clone() for c in Cs], tr, 1.0, -1.0, v)
+        torch.cuda.synchronize()
+        first = first or out
+        for o, f, r, bd in zip(out, first, ref, bnd):
+            assert np.all(np.abs(o.cpu().numpy() - r) <= bd)
+            assert torch.equal(o, f)
