@@ -125,6 +125,7 @@ struct Handle {
   // ULV root LU with partial pivoting (device data)
   double* root_lu = nullptr;
   int* root_piv = nullptr;
+  int* root_pos = nullptr;  // where the LU's row interchanges leave each row
   int* root_info = nullptr;
   int root_m = 0;
   long long generator_bytes() const;

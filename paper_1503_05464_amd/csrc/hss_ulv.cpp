@@ -529,10 +529,24 @@ hss_status factor_impl(Handle& H, hipStream_t s) {
   }
   CHK(prepare_q(H, s));
   int info = 0;
+  std::vector<int> piv(m), row(m), pos(m);
   HIPCHK(hipMemcpyAsync(&info, H.root_info, 4, hipMemcpyDeviceToHost, s));
+  if (m > 0) HIPCHK(hipMemcpyAsync(piv.data(), H.root_piv, (size_t)m * 4, hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
   H.staging.reset();
   if (info != 0) return set_error(HSS_ERR_SINGULAR, "zero pivot in the root LU at column " + std::to_string(info));
+  // where the interchanges leave each row: the solves write the root's
+  // right-hand side there (the interchanges themselves, 64 at a time on the
+  // solve's stream, took 18 us a launch, 42 launches at m = 2700)
+  for (int q = 0; q < m; ++q) row[q] = q;
+  for (int q = 0; q < m; ++q) std::swap(row[q], row[piv[q]]);
+  for (int q = 0; q < m; ++q) pos[row[q]] = q;
+  H.root_pos = static_cast<int*>(H.gen->alloc((size_t)std::max(1, m) * 4));
+  if (!H.root_pos) return set_error(HSS_ERR_ALLOC, "root permutation");
+  if (m > 0) {
+    HIPCHK(hipMemcpyAsync(H.root_pos, pos.data(), (size_t)m * 4, hipMemcpyHostToDevice, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
   H.factored = true;
   return HSS_OK;
 }
@@ -568,13 +582,17 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
   std::vector<GemmDesc> gd;
 
   // right-hand side of an inner node (or the root) into dst:
-  // [bt_{a;b} - W_{a;b} Q_{a;t}^T y_a - B_ab z_b ; bt_{b;b} - B_ba z_a - W_{b;b} Q_{b;t}^T y_b]
-  auto rhs_inner = [&](int t, double* dst, std::vector<GemmDesc>& first, std::vector<GemmDesc>& second) {
+  // [bt_{a;b} - W_{a;b} Q_{a;t}^T y_a - B_ab z_b ; bt_{b;b} - B_ba z_a - W_{b;b} Q_{b;t}^T y_b],
+  // its row i in row pos[i] of dst when a permutation is given
+  auto rhs_inner = [&](int t, double* dst, const int* pos, std::vector<GemmDesc>& first,
+                       std::vector<GemmDesc>& second) {
     const Node& v = nd[t];
     const Node& a = nd[v.left];
     const Node& c = nd[v.right];
     const int ma = md_of(a), mc_ = md_of(c);
     const int ra = ma - a.kr, rc = mc_ - c.kr;
+    double* bot = pos ? dst : dst + (long long)a.kr * nrhs;
+    const int* bpos = pos ? pos + a.kr : nullptr;
     GemmDesc g{};
     g.N = nrhs;
     g.alpha = -1.0;
@@ -586,7 +604,7 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
     g.lda = ma;
     g.B = seg(Tp(v.left), nrhs);
     g.C = seg(Tp(v.left) + (long long)ra * nrhs, nrhs);
-    g.D = out(dst, nrhs);
+    g.D = out(dst, nrhs, pos);
     if (g.M) first.push_back(g);
     // bottom: bt_{b;b} - (W_b Q^T)_b[:, 0:rc] y_b
     g.M = c.kr;
@@ -595,7 +613,7 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
     g.lda = mc_;
     g.B = seg(Tp(v.right), nrhs);
     g.C = seg(Tp(v.right) + (long long)rc * nrhs, nrhs);
-    g.D = out(dst + (long long)a.kr * nrhs, nrhs);
+    g.D = out(bot, nrhs, bpos);
     if (g.M) first.push_back(g);
     // - B_ab z_b, - B_ba z_a
     GemmDesc e{};
@@ -607,16 +625,16 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
     e.A = v.B12;
     e.lda = c.kc;
     e.B = seg(Zp(v.right), nrhs);
-    e.C = seg(dst, nrhs);
-    e.D = out(dst, nrhs);
+    e.C = seg(dst, nrhs, pos);
+    e.D = out(dst, nrhs, pos);
     if (e.M && e.K) second.push_back(e);
     e.M = c.kr;
     e.K = a.kc;
     e.A = v.B21;
     e.lda = a.kc;
     e.B = seg(Zp(v.left), nrhs);
-    e.C = seg(dst + (long long)a.kr * nrhs, nrhs);
-    e.D = out(dst + (long long)a.kr * nrhs, nrhs);
+    e.C = seg(bot, nrhs, bpos);
+    e.D = out(bot, nrhs, bpos);
     if (e.M && e.K) second.push_back(e);
   };
 
@@ -627,7 +645,7 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
       for (int t : lvl) {
         const Node& v = nd[t];
         if (v.leaf()) first.push_back(copy_desc(v.size(), nrhs, seg(b + (long long)v.lo * ldb, ldb), out(Bp(t), nrhs)));
-        else rhs_inner(t, Bp(t), first, second);
+        else rhs_inner(t, Bp(t), nullptr, first, second);
       }
       HIPCHK(launch_gemm_batched(first.data(), (int)first.size(), H.staging, s));
       HIPCHK(launch_gemm_batched(second.data(), (int)second.size(), H.staging, s));
@@ -700,16 +718,14 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
       HIPCHK(launch_gemm_batched(gz.data(), (int)gz.size(), H.staging, s));
     }
     std::vector<GemmDesc> first, second;
-    rhs_inner(0, RB, first, second);
+    rhs_inner(0, RB, H.root_pos, first, second);
     HIPCHK(launch_gemm_batched(first.data(), (int)first.size(), H.staging, s));
     HIPCHK(launch_gemm_batched(second.data(), (int)second.size(), H.staging, s));
   } else {
-    GemmDesc g = copy_desc(m0, nrhs, seg(b, ldb), out(RB, nrhs));
+    GemmDesc g = copy_desc(m0, nrhs, seg(b, ldb), out(RB, nrhs, H.root_pos));
     HIPCHK(launch_gemm_batched(&g, 1, H.staging, s));
   }
-  // root: x_root = U^{-1} L^{-1} P b_root
-  for (int j0 = 0; j0 < m0; j0 += 64)
-    HIPCHK(launch_lu_swap(RB, nrhs, nrhs, H.root_piv, j0, std::min(64, m0 - j0), 0, 0, s));
+  // root: x_root = U^{-1} L^{-1} P b_root (RB holds P b_root)
   if (m0 > 0) {
     std::vector<TriJob> tj{TriJob{H.root_lu, m0, RB, nrhs, m0, nrhs}};
     CHK(tri_solve_batch(tj, true, true, H.staging, s));

@@ -27,7 +27,7 @@
 // address arithmetic), B through addresses looked up ahead in LDS, one
 // barrier per slice that waits for LDS only.  A matvec with 64 columns at n = 20011:
 // 1077 -> 515 us; the class of the widest, longest products (384 + 6 of up to
-// 600 x 256 x 632): 655 -> 545 us.
+// 600 x 256 x 632): 655 -> 527 us.
 #include <algorithm>
 #include <climits>
 #include <cstdlib>

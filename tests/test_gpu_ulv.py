@@ -195,3 +195,27 @@ def test_persistent_slot_ring_matches_exchange_every_step(n, monkeypatch, capfd)
     assert slots[0] and set(slots[0]) == {2}
     assert slots[1] and max(slots[1]) >= 4
     assert torch.equal(xs[0], xs[1])
+
+
+@pytest.mark.parametrize("nrhs", [1, 5, 64])
+@pytest.mark.parametrize("n", [1, 7, 8, 63, 64, 65, 130])
+def test_root_solve_sizes_and_range(n, nrhs):
+    """Root LU of a matrix of one leaf (A = D), whose rows are interchanged
+    by its pivoting, around the 64-row blocks and 8-step groups of the
+    triangular solves: the error of an LU solve is at most about
+    n u cond(A) |x| (growth factors of random matrices are O(1) in practice,
+    10 taken).  The same system scaled by 2^520, whose diagonal is beyond the
+    range of the reciprocal division, gives the same bits."""
+    g = np.random.default_rng(n)
+    A = g.standard_normal((n, n))
+    b = g.standard_normal((n, nrhs))
+    print(f"root solve n={n} nrhs={nrhs}", flush=True)
+    xs = []
+    for scale in (1.0, 2.0 ** 520):
+        h = P.hss_compress(torch.from_numpy(A * scale).cuda(), leaf_size=256)
+        P.hss_factor(h)
+        xs.append(P.hss_solve(h, torch.from_numpy(b * scale).cuda()).cpu().numpy())
+    ref = np.linalg.solve(A, b)
+    err = np.linalg.norm(xs[0] - ref, axis=0) / np.linalg.norm(ref, axis=0)
+    assert np.all(err <= 10 * n * 2.0 ** -53 * np.linalg.cond(A)), err.max()
+    assert np.array_equal(xs[0], xs[1])
