@@ -402,7 +402,7 @@ hipError_t Staging::init(size_t bytes, hipStream_t s) {
   size_t b = (size_t)1 << 20;
   while (b < bytes) b <<= 1;
   stream = s;
-  used = 0;
+  used = copied = 0;
   stream_used = false;
   // a retired block whose readers have run, or, with too many retired
   // blocks (many stream-ordered calls queued and not yet run), the oldest
@@ -452,12 +452,12 @@ hipError_t Staging::retire() {
   if (e != hipSuccess) {  // cannot fence: wait instead, and keep the block
     if (ev) (void)hipEventDestroy(ev);
     e = hipStreamSynchronize(stream);
-    used = 0;
+    used = copied = 0;
     return e;
   }
   spares.push_back(Spare{host, dev, cap, ev});
   host = dev = nullptr;
-  cap = used = 0;
+  cap = used = copied = 0;
   stream_used = false;
   return hipSuccess;
 }
@@ -481,6 +481,8 @@ void Staging::release() {
 // a block of at least `need` bytes with nothing pushed yet
 static bool fresh_block(Staging& st, size_t need) {
   if (st.host && st.used == 0 && need <= st.cap) return true;
+  if (st.deferred && st.issue() != hipSuccess) return false;  // launches noted on this block's tables
+  st.copied = 0;
   if (st.host && st.retire() != hipSuccess) return false;
   if (st.host && need <= st.cap) return true;  // retire fell back to a wait
   if (st.host) {  // too small: give it back
@@ -499,12 +501,30 @@ void* Staging::push(const void* src, size_t bytes) {
     if (!fresh_block(*this, need)) return nullptr;
   }
   std::memcpy(host + used, src, bytes);
-  stream_used = true;
-  if (hipMemcpyAsync(dev + used, host + used, bytes, hipMemcpyHostToDevice, stream) != hipSuccess)
-    return nullptr;
+  if (!deferred) {
+    stream_used = true;
+    if (hipMemcpyAsync(dev + used, host + used, bytes, hipMemcpyHostToDevice, stream) != hipSuccess)
+      return nullptr;
+  }
   void* r = dev + used;
   used += need;
   return r;
+}
+
+hipError_t Staging::issue() {
+  if (host && used > copied) {
+    stream_used = true;
+    const hipError_t e = hipMemcpyAsync(dev + copied, host + copied, used - copied, hipMemcpyHostToDevice, stream);
+    if (e != hipSuccess) return e;
+    copied = used;
+  }
+  for (auto& f : noted) {
+    const hipError_t e = f();
+    if (e != hipSuccess) return e;
+  }
+  noted.clear();
+  batch = std::min<size_t>(batch * 2, 256);
+  return hipSuccess;
 }
 
 bool Staging::reserve(std::initializer_list<size_t> sizes) {
@@ -1424,10 +1444,10 @@ struct MvJob {
 // Alg. 2 for several handles at once: every phase (upward sweep of a height,
 // downward sweep of a height, leaves) is one batched GEMM launch over all of
 // them, heights aligned from the leaves.  Workspace and descriptor staging
-// come from the lead handle L.  Host-synchronous at the end (the descriptor
-// tables live in the staging area until their copies ran).
+// come from the lead handle L; the tables of the phases share a few copies.
 hss_status matvec_many(Handle& L, std::vector<MvJob>& jobs, hipStream_t s) {
   L.staging.stream = s;
+  Deferred defer(L.staging);
   // workspace: y (kc), z (kr), w (mr) per node and job, nrhs columns each
   std::vector<std::vector<long long>> oy(jobs.size()), oz(jobs.size()), ow(jobs.size());
   long long tot = 0;
@@ -1622,6 +1642,7 @@ hss_status matvec_many(Handle& L, std::vector<MvJob>& jobs, hipStream_t s) {
     }
   }
   HIPCHK(flush());
+  HIPCHK(defer.done());
   // stream-ordered: the descriptor tables stay in their staging block until
   // the work queued so far has run
   HIPCHK(L.staging.retire());

@@ -2,6 +2,7 @@
 // kernels of the randomized HSS library (gfx950).
 #pragma once
 
+#include <functional>
 #include <initializer_list>
 #include <vector>
 
@@ -34,6 +35,26 @@ struct Staging {
     hipEvent_t ev;
   };
   std::vector<Spare> spares;
+  // While deferred, push() only fills the pinned block and launch() only
+  // notes the launch: a run of small launches then pays one copy instead of
+  // one each (a copy of any size takes 2 to 5 us on the stream, as long as a
+  // small kernel).  The copies are issued with the launches after 4 notes,
+  // then 8, 16, ..., so that the device starts while the host still builds
+  // the later tables.
+  bool deferred = false;
+  size_t copied = 0;  // bytes of the block whose copies were queued
+  size_t batch = 4;   // launches noted before they are issued
+  std::vector<std::function<hipError_t()>> noted;
+  // Runs f (a kernel launch, or anything queued on `stream`) now, or when
+  // the launches noted before it are issued.
+  template <typename F>
+  hipError_t launch(F&& f) {
+    if (!deferred) return f();
+    noted.emplace_back(std::forward<F>(f));
+    return noted.size() >= batch ? issue() : hipSuccess;
+  }
+  // One copy of everything pushed since the last one, then the noted launches.
+  hipError_t issue();
   // Takes a block of at least `bytes` (a retired one whose readers have run,
   // or a new one).
   hipError_t init(size_t bytes, hipStream_t s);
@@ -49,11 +70,34 @@ struct Staging {
   // block happens here, before the first of them.  False on failure.
   bool reserve(std::initializer_list<size_t> sizes);
   // The caller has synchronised the stream: the block is free again.
-  void reset() { used = 0; }
+  void reset() { used = copied = 0; }
   // Ends a stream-ordered call without waiting: the tables pushed so far stay
   // valid until the work queued on `stream` up to now has run; the next push
   // goes to another block.
   hipError_t retire();
+};
+
+// Defers st's copies and launches while it lives.  done() issues what is left;
+// without it (an error return) what is left is dropped.
+struct Deferred {
+  Staging& st;
+  explicit Deferred(Staging& s) : st(s) {
+    st.deferred = true;
+    st.copied = st.used;
+    st.batch = 4;
+    st.noted.clear();
+  }
+  hipError_t done() {
+    const hipError_t e = st.issue();
+    st.deferred = false;
+    return e;
+  }
+  ~Deferred() {
+    st.deferred = false;
+    st.noted.clear();
+  }
+  Deferred(const Deferred&) = delete;
+  Deferred& operator=(const Deferred&) = delete;
 };
 
 // ---------------------------------------------------------------------------

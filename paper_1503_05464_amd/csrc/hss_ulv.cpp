@@ -64,6 +64,13 @@ GemmDesc copy_desc(int M, int N, const Seg& src, const SegOut& dst) {
 
 int md_of(const Node& v) { return v.leaf() ? v.size() : v.mr; }
 
+// The handle's scratch buffer, at least `bytes` long.  Growing it frees the
+// old block, so launches noted on the staging area (deferred) go out first.
+double* misc_work(Handle& H, size_t bytes, hipStream_t s) {
+  if (bytes + 256 > H.work_misc.cap && H.staging.issue() != hipSuccess) return nullptr;
+  return static_cast<double*>(H.work_misc.ensure(bytes, s));
+}
+
 // Blocked triangular solve X <- T^{-1} X for a batch: lower (forward) or
 // upper (backward) T of order n (ld ldt), X n x nrhs (ld ldx).
 struct TriJob {
@@ -169,7 +176,7 @@ hss_status apply_q_blocked(Handle& H, const std::vector<ReflDesc>& rd, hipStream
   for (const ReflDesc& d : rd) pre = pre && d.Y && d.T;
   const long long og = tot;
   if (!pre) tot += 2LL * nbtot * 64 * 64;
-  double* ws = static_cast<double*>(H.work_misc.ensure((size_t)tot * 8 + 8, s));
+  double* ws = misc_work(H, (size_t)tot * 8 + 8, s);
   if (!ws) return set_error(HSS_ERR_ALLOC, "reflector workspace");
   auto Y = [&](size_t p) -> const double* { return pre ? rd[p].Y : ws + oy[p]; };
   auto Tb = [&](size_t p, int b) -> const double* {
@@ -327,7 +334,7 @@ hss_status prepare_q(Handle& H, hipStream_t s) {
     gtot += (long long)nb * 64 * 64;
   }
   if (yd.empty()) return HSS_OK;
-  double* G = static_cast<double*>(H.work_misc.ensure((size_t)gtot * 8 + 8, s));
+  double* G = misc_work(H, (size_t)gtot * 8 + 8, s);
   if (!G) return set_error(HSS_ERR_ALLOC, "reflector workspace");
   HIPCHK(launch_refl_y(yd.data(), (int)yd.size(), rmax, mmax, H.staging, s));
   long long go = 0;
@@ -506,10 +513,11 @@ hss_status factor_impl(Handle& H, hipStream_t s) {
   // in one workgroup, the GEMM below the rest on the whole device (N=32768
   // serving factor 65.9 ms with panels of 64, 62.2 with 32, 63.4 with 16)
   constexpr int PW = 32;
+  Deferred defer(H.staging);
   for (int j0 = 0; j0 < m; j0 += PW) {
     const int nb = std::min(PW, m - j0), j1 = j0 + nb;
-    HIPCHK(launch_lu_panel(H.root_lu, m, m, j0, nb, H.root_piv, H.root_info, s));
-    HIPCHK(launch_lu_swap(H.root_lu, m, m, H.root_piv, j0, nb, j0, j1, s));
+    HIPCHK(launch_lu_panel(H.root_lu, m, m, j0, nb, H.root_piv, H.root_info, H.staging, s));
+    HIPCHK(launch_lu_swap(H.root_lu, m, m, H.root_piv, j0, nb, j0, j1, H.staging, s));
     if (j1 < m) {
       std::vector<TriJob> tj{TriJob{H.root_lu + (long long)j0 * m + j0, m, H.root_lu + (long long)j0 * m + j1,
                                     m, nb, m - j1}};
@@ -528,6 +536,7 @@ hss_status factor_impl(Handle& H, hipStream_t s) {
     }
   }
   CHK(prepare_q(H, s));
+  HIPCHK(defer.done());
   int info = 0;
   std::vector<int> piv(m), row(m), pos(m);
   HIPCHK(hipMemcpyAsync(&info, H.root_info, 4, hipMemcpyDeviceToHost, s));
@@ -555,6 +564,7 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
                       hipStream_t s) {
   std::vector<Node>& nd = H.nodes;
   H.staging.stream = s;
+  Deferred defer(H.staging);
   const int m0 = H.root_m;
   // workspace: per node B (md x nrhs), T (md x nrhs), z (kc x nrhs), X (md x nrhs); root RB
   std::vector<long long> oB(nd.size()), oT(nd.size()), oz(nd.size()), oX(nd.size());
@@ -762,6 +772,7 @@ hss_status solve_impl(Handle& H, int nrhs, const double* b, long long ldb, doubl
       CHK(apply_q_blocked(H, rd, s));
     }
   }
+  HIPCHK(defer.done());
   // stream-ordered: the descriptor tables stay in their staging block until
   // the work queued so far has run
   HIPCHK(H.staging.retire());

@@ -64,8 +64,8 @@ hipError_t launch_larft(const LarftDesc* d, int nd, Staging& st, hipStream_t s);
 hipError_t launch_vt_leaf(const VtLeafDesc* d, int nd, int kmax, Staging& st, hipStream_t s);
 hipError_t launch_tri_block(const TriDesc* d, int nd, Staging& st, hipStream_t s);
 hipError_t launch_lu_panel(double* A, long long ld, int n, int j0, int nb, int* piv, int* info,
-                           hipStream_t s);
+                           Staging& st, hipStream_t s);
 hipError_t launch_lu_swap(double* A, long long ld, int ncols, const int* piv, int j0, int nb,
-                          int skip0, int skip1, hipStream_t s);
+                          int skip0, int skip1, Staging& st, hipStream_t s);
 
 }  // namespace hss

@@ -386,9 +386,13 @@ hipError_t launch_gemm_batched(const GemmDesc* descs, int nprob, Staging& st, hi
   std::memcpy(table.data() + db, tile0.data(), tb);
   char* dd = static_cast<char*>(st.push(table.data(), db + tb));
   if (!dd) return hipErrorOutOfMemory;
-  hipLaunchKernelGGL(gv.fn, dim3((unsigned)tiles), dim3(NTH), 0, s, reinterpret_cast<const DevDesc*>(dd),
-                     reinterpret_cast<const long long*>(dd + db), (int)h.size());
-  return hipGetLastError();
+  const auto fn = gv.fn;
+  const int np = (int)h.size();
+  return st.launch([=] {
+    hipLaunchKernelGGL(fn, dim3((unsigned)tiles), dim3(NTH), 0, s, reinterpret_cast<const DevDesc*>(dd),
+                       reinterpret_cast<const long long*>(dd + db), np);
+    return hipGetLastError();
+  });
 }
 
 int gemm_variants() { return kNumGVariants; }

@@ -532,8 +532,10 @@ hipError_t launch_vt_leaf(const VtLeafDesc* d, int nd, int kmax, Staging& st, hi
   if (nd <= 0 || kmax <= 0) return hipSuccess;
   const VtLeafDesc* dd = static_cast<const VtLeafDesc*>(st.push(d, sizeof(VtLeafDesc) * nd));
   if (!dd) return hipErrorOutOfMemory;
-  hipLaunchKernelGGL(vt_leaf_kernel, dim3(kmax, nd), dim3(NT), 0, s, dd);
-  return hipGetLastError();
+  return st.launch([=] {
+    hipLaunchKernelGGL(vt_leaf_kernel, dim3(kmax, nd), dim3(NT), 0, s, dd);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_tri_block(const TriDesc* d, int nd, Staging& st, hipStream_t s) {
@@ -545,13 +547,15 @@ hipError_t launch_tri_block(const TriDesc* d, int nd, Staging& st, hipStream_t s
   }
   const TriDesc* dd = static_cast<const TriDesc*>(st.push(d, sizeof(TriDesc) * nd));
   if (!dd) return hipErrorOutOfMemory;
-  if (cmax <= kTriWaveMaxRhs)
-    hipLaunchKernelGGL(tri_wave_kernel, dim3(nd, (cmax + 3) / 4), dim3(NT), 0, s, dd);
-  else if (nbmax <= 32)
-    hipLaunchKernelGGL(tri_block_kernel<32>, dim3(nd, (cmax + NT - 1) / NT), dim3(NT), 0, s, dd);
-  else
-    hipLaunchKernelGGL(tri_block_kernel<64>, dim3(nd, (cmax + NT - 1) / NT), dim3(NT), 0, s, dd);
-  return hipGetLastError();
+  return st.launch([=] {
+    if (cmax <= kTriWaveMaxRhs)
+      hipLaunchKernelGGL(tri_wave_kernel, dim3(nd, (cmax + 3) / 4), dim3(NT), 0, s, dd);
+    else if (nbmax <= 32)
+      hipLaunchKernelGGL(tri_block_kernel<32>, dim3(nd, (cmax + NT - 1) / NT), dim3(NT), 0, s, dd);
+    else
+      hipLaunchKernelGGL(tri_block_kernel<64>, dim3(nd, (cmax + NT - 1) / NT), dim3(NT), 0, s, dd);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_refl_y(const ReflYDesc* d, int nd, int rmax, int mmax, Staging& st, hipStream_t s) {
@@ -559,8 +563,10 @@ hipError_t launch_refl_y(const ReflYDesc* d, int nd, int rmax, int mmax, Staging
   const ReflYDesc* dd = static_cast<const ReflYDesc*>(st.push(d, sizeof(ReflYDesc) * nd));
   if (!dd) return hipErrorOutOfMemory;
   const int tiles = ((mmax + 63) / 64) * ((rmax + 63) / 64);
-  hipLaunchKernelGGL(refl_y_kernel, dim3(tiles, nd), dim3(NT), 0, s, dd);
-  return hipGetLastError();
+  return st.launch([=] {
+    hipLaunchKernelGGL(refl_y_kernel, dim3(tiles, nd), dim3(NT), 0, s, dd);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_sum_partials(const SumDesc* d, int nd, Staging& st, hipStream_t s) {
@@ -569,42 +575,50 @@ hipError_t launch_sum_partials(const SumDesc* d, int nd, Staging& st, hipStream_
   for (int i = 0; i < nd; ++i) emax = std::max(emax, d[i].rows * d[i].cols);
   const SumDesc* dd = static_cast<const SumDesc*>(st.push(d, sizeof(SumDesc) * nd));
   if (!dd) return hipErrorOutOfMemory;
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((emax + NT - 1) / NT, nd), dim3(NT), 0, s, dd);
-  return hipGetLastError();
+  return st.launch([=] {
+    hipLaunchKernelGGL(sum_partials_kernel, dim3((emax + NT - 1) / NT, nd), dim3(NT), 0, s, dd);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_larft(const LarftDesc* d, int nd, Staging& st, hipStream_t s) {
   if (nd <= 0) return hipSuccess;
   const LarftDesc* dd = static_cast<const LarftDesc*>(st.push(d, sizeof(LarftDesc) * nd));
   if (!dd) return hipErrorOutOfMemory;
-  hipLaunchKernelGGL(larft_kernel, dim3(nd), dim3(64), 0, s, dd);
-  return hipGetLastError();
+  return st.launch([=] {
+    hipLaunchKernelGGL(larft_kernel, dim3(nd), dim3(64), 0, s, dd);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_lu_panel(double* A, long long ld, int n, int j0, int nb, int* piv, int* info,
-                           hipStream_t s) {
+                           Staging& st, hipStream_t s) {
   const int rows = n - j0;
-  if (nb > 64 || rows > 4096)
-    hipLaunchKernelGGL(lu_panel_kernel, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
-  else if (rows > 2048)
-    hipLaunchKernelGGL(lu_panel_reg_kernel<4>, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
-  else if (rows > 1024)
-    hipLaunchKernelGGL(lu_panel_reg_kernel<2>, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
-  else if (rows > 512)
-    hipLaunchKernelGGL(lu_panel_reg_kernel<1>, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
-  else if (rows > 256)
-    hipLaunchKernelGGL((lu_panel_reg_kernel<2, 256>), dim3(1), dim3(256), 0, s, A, ld, n, j0, nb, piv, info);
-  else
-    hipLaunchKernelGGL((lu_panel_reg_kernel<1, 256>), dim3(1), dim3(256), 0, s, A, ld, n, j0, nb, piv, info);
-  return hipGetLastError();
+  return st.launch([=] {
+    if (nb > 64 || rows > 4096)
+      hipLaunchKernelGGL(lu_panel_kernel, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
+    else if (rows > 2048)
+      hipLaunchKernelGGL(lu_panel_reg_kernel<4>, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
+    else if (rows > 1024)
+      hipLaunchKernelGGL(lu_panel_reg_kernel<2>, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
+    else if (rows > 512)
+      hipLaunchKernelGGL(lu_panel_reg_kernel<1>, dim3(1), dim3(1024), 0, s, A, ld, n, j0, nb, piv, info);
+    else if (rows > 256)
+      hipLaunchKernelGGL((lu_panel_reg_kernel<2, 256>), dim3(1), dim3(256), 0, s, A, ld, n, j0, nb, piv, info);
+    else
+      hipLaunchKernelGGL((lu_panel_reg_kernel<1, 256>), dim3(1), dim3(256), 0, s, A, ld, n, j0, nb, piv, info);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_lu_swap(double* A, long long ld, int ncols, const int* piv, int j0, int nb,
-                          int skip0, int skip1, hipStream_t s) {
+                          int skip0, int skip1, Staging& st, hipStream_t s) {
   if (ncols <= 0 || nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(lu_swap_kernel, dim3((ncols + NT - 1) / NT), dim3(NT), 0, s, A, ld, ncols, piv,
-                     j0, nb, skip0, skip1);
-  return hipGetLastError();
+  return st.launch([=] {
+    hipLaunchKernelGGL(lu_swap_kernel, dim3((ncols + NT - 1) / NT), dim3(NT), 0, s, A, ld, ncols, piv,
+                       j0, nb, skip0, skip1);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace hss
