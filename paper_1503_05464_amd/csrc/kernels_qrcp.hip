@@ -206,29 +206,52 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
 #pragma unroll
   for (int c = 0; c < N; ++c) v[c] += __shfl_xor(v[c], 32, 64);
 }
+
+// The same N <= 16 sums, bit for bit, spread over the lanes: lane l returns
+// the sum of value l % P, P the power of two not below N (lanes whose value
+// would be N or more hold another value's sum).  At each of the first
+// four levels a lane keeps one value of a pair and hands the other to its
+// partner, so the number of values halves; every level adds the same two
+// partial sums as the butterfly above.  62 instructions for N = 8 against
+// 176 for eight butterflies, in a loop that is bound by its instructions.
+constexpr int sums_period(int n) { return n > 8 ? 16 : n > 4 ? 8 : n > 2 ? 4 : n > 1 ? 2 : 1; }
+template <int B>  // the value of lane l ^ B
+__device__ __forceinline__ double lane_xor(double v) {
+  if (B == 1) return dpp_d<0xB1>(v);
+  if (B == 2) return dpp_d<0x4E>(v);
+  if (B == 8) return dpp_d<0x128>(v);   // row_ror 8
+  return dpp_d<0x1B>(dpp_d<0x141>(v));  // 7 - l, then 3 - l within quads: l ^ 4
+}
+template <int B, int N>
+__device__ __forceinline__ void fold_pairs(const double (&v)[N], double (&o)[(N + 1) / 2], int lane) {
+  const bool up = (lane & B) != 0;
+#pragma unroll
+  for (int j = 0; j < N / 2; ++j) {
+    const double mine = up ? v[2 * j + 1] : v[2 * j];
+    const double other = up ? v[2 * j] : v[2 * j + 1];
+    o[j] = mine + lane_xor<B>(other);
+  }
+  if (N & 1) o[N / 2] = v[N - 1] + lane_xor<B>(v[N - 1]);
+}
 template <int N>
-__device__ __forceinline__ void wave_sum_n_pl(double (&v)[N]) {
-#pragma unroll
-  for (int c = 0; c < N; ++c) v[c] += dpp_d<0xB1>(v[c]);
-#pragma unroll
-  for (int c = 0; c < N; ++c) v[c] += dpp_d<0x4E>(v[c]);
-#pragma unroll
-  for (int c = 0; c < N; ++c) v[c] += dpp_d<0x141>(v[c]);
-#pragma unroll
-  for (int c = 0; c < N; ++c) v[c] += dpp_d<0x140>(v[c]);
-  // own + partner in either order: the same sum (addition commutes)
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    double a, b;
-    cross_pair<16>(v[c], a, b);
-    v[c] = a + b;
-  }
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    double a, b;
-    cross_pair<32>(v[c], a, b);
-    v[c] = a + b;
-  }
+__device__ __forceinline__ double wave_sums_spread(const double (&v)[N], int lane) {
+  static_assert(N <= 16, "four levels");
+  constexpr int N1 = (N + 1) / 2, N2 = (N1 + 1) / 2, N3 = (N2 + 1) / 2;
+  double a[N1], b[N2], c[N3], d[1];
+  fold_pairs<1, N>(v, a, lane);
+  fold_pairs<2, N1>(a, b, lane);
+  fold_pairs<4, N2>(b, c, lane);
+  fold_pairs<8, N3>(c, d, lane);
+  double x, y;  // own + partner in either order: the same sum (addition commutes)
+  cross_pair<16>(d[0], x, y);
+  double r = x + y;
+  cross_pair<32>(r, x, y);
+  return x + y;
+}
+// lane l's value (a literal lane) to every lane, as a scalar
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
 // wavefront sum of one value, by the same butterfly (four DPP levels, two
@@ -260,11 +283,20 @@ __device__ __forceinline__ void wave_argmax(double& bv, int& bi) {
   better(bv, bi, __shfl_xor(bv, 16, 64), __shfl_xor(bi, 16, 64));
   better(bv, bi, __shfl_xor(bv, 32, 64), __shfl_xor(bi, 32, 64));
 }
-__device__ __forceinline__ void wave_argmax_pl(double& bv, int& bi) {
-  better(bv, bi, dpp_d<0xB1>(bv), dpp_i<0xB1>(bi));
-  better(bv, bi, dpp_d<0x4E>(bv), dpp_i<0x4E>(bi));
-  better(bv, bi, dpp_d<0x141>(bv), dpp_i<0x141>(bi));
+// the best pair of each group of P lanes (1, 2, 4, 8 or 16), in all of them
+template <int P>
+__device__ __forceinline__ void group_argmax(double& bv, int& bi) {
+  if (P > 1) better(bv, bi, dpp_d<0xB1>(bv), dpp_i<0xB1>(bi));
+  if (P > 2) better(bv, bi, dpp_d<0x4E>(bv), dpp_i<0x4E>(bi));
+  if (P > 4) better(bv, bi, dpp_d<0x141>(bv), dpp_i<0x141>(bi));
+  if (P > 8) better(bv, bi, dpp_d<0x140>(bv), dpp_i<0x140>(bi));
+}
+// the best pair of lanes 0..n-1 in lane 0 (in every lane for n > 16); n uniform
+__device__ __forceinline__ void first_argmax(double& bv, int& bi, int n) {
+  group_argmax<8>(bv, bi);
+  if (n <= 8) return;
   better(bv, bi, dpp_d<0x140>(bv), dpp_i<0x140>(bi));
+  if (n <= 16) return;
   // across rows: the better of {own, partner} in either order (a total order)
   double av, cv;
   int ai, ci;
@@ -964,6 +996,14 @@ __global__ __launch_bounds__(ST) void id_step_kernel(const DevProb* __restrict__
 // values as the reflector and updates its own columns.  Per step, global
 // memory carries only the candidates and one column per workgroup.
 //
+// A step is a chain: records out and in (1.0 us), the best of them (0.35),
+// the winner's column (0.45 + 0.2 into LDS), the dots, their sums, the
+// update, the norms' sums, this workgroup's best.  The arithmetic is bound
+// by its instructions (two wavefronts per SIMD), so the sums are spread over
+// lanes and the reductions over pairs take three levels of lanes rather than
+// eight values in turn: 7.0 us before, 4.4 us a step at 512 rows x 8 columns
+// per wavefront, 5.6 at 1024 x 6 (28 workgroups).
+//
 // Every word that crosses workgroups carries the step it belongs to, so a
 // reader can tell a current word from a stale one by looking at the word
 // alone; no ordering between different words is needed, hence no fences
@@ -998,18 +1038,17 @@ __device__ __forceinline__ V ld_dev(const V* p) {
 }
 
 // The step loop is written for the register allocator: slices are skipped
-// in groups of PG (a handful of uniform branches per step, the finished
+// in groups of PG = 4 or 3 (a handful of uniform branches per step, the finished
 // rows of a processed group see u = 0), at most PG reflector values are
 // read from LDS ahead of their use, and the published column's addresses are
 // formed inside the loop.  Each wavefront keeps only its best remaining
 // column's norm, not one per column.
-constexpr int PG = 4;
-
 template <int T, int C>
 __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restrict__ probs,
                                                          const int* __restrict__ wg_prob,
                                                          double rtol, Work w) {
-  static_assert(T % PG == 0, "slices are skipped PG at a time");
+  constexpr int PG = T % 4 == 0 ? 4 : 3;
+  static_assert(T % PG == 0 && C <= 16, "slices are skipped PG at a time; sums of at most 16 columns");
   constexpr int SU = (T * 64 + PT - 1) / PT;  // reflector rows staged per thread
   __shared__ double u[T * 64];
   __shared__ double rv[PW];
@@ -1047,6 +1086,8 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
   double y[C][T];
   double bv = -1.0;  // this wavefront's best remaining column: norm, index
   int bi = INT_MAX;
+  constexpr int SP = sums_period(C);
+  const int lc = lane & (SP - 1);  // the column whose sums this lane holds (if below C)
   unsigned sel = 0;  // columns of this wavefront already chosen as pivots
 #pragma unroll
   for (int c = 0; c < C; ++c) {
@@ -1060,7 +1101,8 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
       y[c][t] = v;
       s = fma(v, v, s);
     }
-    if (nopiv ? j == 0 : j < m) better(bv, bi, wave_sum(s), j);  // squared norms throughout
+    s = wave_sum(s);  // squared norms throughout
+    if (nopiv ? j == 0 : j < m) better(bv, bi, nopiv && !(s >= 0.0) ? 0.0 : s, j);
     if (j < m && lane == 0) step[j] = -1;
     asm volatile("" ::: "memory");  // one column's loads in flight at a time
   }
@@ -1081,10 +1123,10 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
       ri[wave] = bi;
     }
     __syncthreads();
-    double v = rv[0];
-    int ix = ri[0];
-#pragma unroll
-    for (int t = 1; t < PW; ++t) better(v, ix, rv[t], ri[t]);
+    double v = rv[lane & (PW - 1)];
+    int ix = ri[lane & (PW - 1)];
+    group_argmax<PW>(v, ix);  // every lane ends with the same pair
+    ix = __builtin_amdgcn_readfirstlane(ix);
     const bool own = ix >= jb && ix < jb + C;  // uniform within a wavefront
     if (lane == 0 && (own || (ix == INT_MAX && wave == 0))) {
       unsigned long long* r = w.rec + 2 * ((long long)blockIdx.x * w.rstride + i);
@@ -1119,7 +1161,8 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
     }
   };
 
-  // wait for the problem's G candidates of step i; false on a timeout
+  // wait for the problem's G candidates of step i; false on a timeout.  The
+  // best pair is (squared norm, column); no candidate: (-1, INT_MAX)
   auto gather = [&](int i, double& best, int& p) __attribute__((always_inline)) -> bool {
     // workgroup-major records: the G records of one step lie in G different
     // cache lines (and memory channels), not packed into a few lines that
@@ -1165,21 +1208,21 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
       if (ok) better(gv, gi, __longlong_as_double((long long)(a ^ kSignBit)), (int)(unsigned)b);
     }
     if (!ok) s_ok = 0;
-    wave_argmax_pl(gv, gi);
     // gv_s / gi_s, not rv / ri: publish has no closing barrier, so another
-    // wavefront may still be reading rv / ri
-    if (lane == 0) {
-      gv_s[wave] = gv;
-      gi_s[wave] = gi;
+    // wavefront may still be reading rv / ri.  Up to 64 records are the first
+    // wavefront's alone: its pair is the workgroup's.
+    const bool one = !full || dp.G <= 64;
+    if (!one || wave == 0) {
+      first_argmax(gv, gi, full ? dp.G : 1);
+      if (lane == 0) {
+        gv_s[wave] = gv;
+        gi_s[wave] = gi;
+      }
     }
     __syncthreads();
-    // every thread reduces the PW wavefront results itself (no second barrier)
-    double v = gv_s[0];
-    int ix = gi_s[0];
-#pragma unroll
-    for (int t = 1; t < PW; ++t) better(v, ix, gv_s[t], gi_s[t]);
-    best = sqrt(fmax(v, 0.0));  // squared norms in the records: the winner's root only
-    p = ix;
+    best = gv_s[one ? 0 : lane & (PW - 1)];
+    p = gi_s[one ? 0 : lane & (PW - 1)];
+    if (!one) group_argmax<PW>(best, p);
     return s_ok != 0;
   };
 
@@ -1192,8 +1235,7 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
     if (!gather(i, best, p)) return;
     // uniform: a scalar base address for the winner's slot below
     p = __builtin_amdgcn_readfirstlane(p);
-    if (i == 0) nu0 = best;
-    if (!nopiv && (best <= 0.0 || best <= rtol * nu0)) break;
+    if (p == INT_MAX) break;  // no candidate left
     if (!nopiv && dp.p.kfail >= 0 && i > dp.p.kfail && m > d) break;
     const int gp = p / CPG;  // the workgroup that published column p
     const unsigned long long* xp = w.cbuf + ((long long)(i & w.rmask) * nslot + dp.g0 + gp) * 2 * ldcb;
@@ -1205,7 +1247,7 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
     // and every thread recovers alpha from v0).
     {
       const unsigned want = (unsigned)(i + 1);
-      unsigned long long wl[SU], wh[SU];
+      bool stop = false;
       const char* xb = reinterpret_cast<const char*>(xp);
       const char* xc = reinterpret_cast<const char*>(xp + ldcb);
       // 32-bit byte offsets from the uniform bases: a scalar base plus one
@@ -1213,32 +1255,51 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
       auto at = [](const char* base, unsigned row) {
         return reinterpret_cast<const unsigned long long*>(base + row * 8u);
       };
+      // rows per thread in flight together: all of them, but one at a time
+      // where the columns leave no registers for more (36 x 3: 16 spilled
+      // registers instead of 55, 1094 against 1129 ms per gauss65536)
+      constexpr int LC = T * C > 96 ? 1 : SU;
 #pragma unroll
-      for (int t = 0; t < SU; ++t) {
-        const int r = tid + PT * t;
-        const unsigned rr = (r >= i && r < d) ? (unsigned)r : (unsigned)i;
-        wl[t] = ld_dev(at(xb, rr));
-        wh[t] = ld_dev(at(xc, rr));
-      }
+      for (int tb = 0; tb < SU; tb += LC) {
+        unsigned long long wl[LC], wh[LC];
 #pragma unroll
-      for (int t = 0; t < SU; ++t) {
-        const int r = tid + PT * t;
-        if (r >= T * 64) break;
-        const bool in = r >= i && r < d;
-        int spins = 0;
-        while (in && ((unsigned)(wl[t] >> 32) != want || (unsigned)(wh[t] >> 32) != want)) {
-          if ((++spins & 63) == 0 && (ld_dev(w.err) || spins >= kSpinLimit)) {
-            st_dev(w.err, 1);
-            s_ok = 0;
+        for (int t = tb; t < SU && t < tb + LC; ++t) {
+          const int r = tid + PT * t;
+          const unsigned rr = (r >= i && r < d) ? (unsigned)r : (unsigned)i;
+          wl[t - tb] = ld_dev(at(xb, rr));
+          wh[t - tb] = ld_dev(at(xc, rr));
+        }
+        if (tb == 0) {
+          // the root and the stopping rule while the loads are in flight
+          __builtin_amdgcn_sched_barrier(0);
+          best = sqrt(fmax(best, 0.0));  // squared norms in the records: the winner's root only
+          if (i == 0) nu0 = best;
+          if (!nopiv && (best <= 0.0 || best <= rtol * nu0)) {
+            stop = true;
             break;
           }
-          __builtin_amdgcn_s_sleep(1);
-          wl[t] = ld_dev(at(xb, (unsigned)r));
-          wh[t] = ld_dev(at(xc, (unsigned)r));
         }
-        const double x = __longlong_as_double((long long)((wh[t] << 32) | (wl[t] & 0xffffffffull)));
-        u[r] = in ? (r == i ? x + copysign(best, x) : x) : 0.0;
+#pragma unroll
+        for (int t = tb; t < SU && t < tb + LC; ++t) {
+          const int r = tid + PT * t;
+          if (r >= T * 64) break;
+          const bool in = r >= i && r < d;
+          int spins = 0;
+          while (in && ((unsigned)(wl[t - tb] >> 32) != want || (unsigned)(wh[t - tb] >> 32) != want)) {
+            if ((++spins & 63) == 0 && (ld_dev(w.err) || spins >= kSpinLimit)) {
+              st_dev(w.err, 1);
+              s_ok = 0;
+              break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+            wl[t - tb] = ld_dev(at(xb, (unsigned)r));
+            wh[t - tb] = ld_dev(at(xc, (unsigned)r));
+          }
+          const double x = __longlong_as_double((long long)((wh[t - tb] << 32) | (wl[t - tb] & 0xffffffffull)));
+          u[r] = in ? (r == i ? x + copysign(best, x) : x) : 0.0;
+        }
       }
+      if (stop) break;
     }
     __syncthreads();
     if (!s_ok) return;  // a wait timed out (flag raised for the whole problem)
@@ -1246,8 +1307,6 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
     // the barriers of publish and gather
     const double v0 = u[i];
     const double alpha = -copysign(best, v0);
-    // H = I - beta v v^T (a zero column, only without pivoting: H = I)
-    const double beta = best > 0.0 ? -1.0 / (alpha * v0) : 0.0;
     if (p >= jb && p < jb + C) {
       sel |= 1u << (p - jb);
       // the owner marks its column: the same wavefront wrote its -1, and
@@ -1278,13 +1337,15 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
         for (int c = 0; c < C; ++c) f[c] = fma(ut, y[c][t], f[c]);
       }
     }
-    wave_sum_n_pl<C>(f);
+    // H = I - beta v v^T (a zero column, only without pivoting: H = I); the
+    // division's chain runs beside the sums'
+    const double beta = best > 0.0 ? -1.0 / (alpha * v0) : 0.0;
+    const bool live = lc < C && !((sel >> lc) & 1u) && jb + lc < m;  // pivots stay as they are
+    double fr = wave_sums_spread<C>(f, lane);
+    fr = live ? beta * fr : 0.0;
     asm volatile("" ::: "memory");  // u is read again below rather than kept in registers
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const bool live = !((sel >> c) & 1u) && jb + c < m;  // pivots stay as they are
-      f[c] = live ? beta * f[c] : 0.0;
-    }
+    for (int c = 0; c < C; ++c) f[c] = lane_value(fr, c);
     // norms of the rows below i: slice i/64 counts the lanes past i only
     double s2[C];
 #pragma unroll
@@ -1307,12 +1368,14 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
         }
       }
     }
-    wave_sum_n_pl<C>(s2);
-    bv = -1.0;
-    bi = INT_MAX;
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-      if (nopiv ? jb + c == i + 1 : (!((sel >> c) & 1u) && jb + c < m)) better(bv, bi, s2[c], jb + c);
+    // this wavefront's best: a NaN is no candidate (without pivoting, where
+    // column i + 1 is the next pivot whatever it holds, it counts as zero)
+    bv = wave_sums_spread<C>(s2, lane);
+    const bool num = bv >= 0.0;
+    const bool cand = nopiv ? lc < C && jb + lc == i + 1 : live && num;
+    bv = cand ? (num ? bv : 0.0) : -1.0;
+    bi = cand ? jb + lc : INT_MAX;
+    group_argmax<SP>(bv, bi);
     k = i + 1;
     if (i + 1 < dp.kmax) publish(i + 1);
   }
@@ -1453,31 +1516,52 @@ static int small_class(const IdProblem& p) {
 }
 
 // Persistent-path variants: T rows per lane (d <= 64 T), C columns per
-// wavefront, sized so that the columns fit in the register file.
+// wavefront, widest first.  The widest of each T holds its columns in
+// architectural registers (up to 96 values per lane; one step wider, 8 x 12,
+// 12 x 8 or 20 x 5, spills or moves through accumulation registers and takes
+// 1.3 to 1.8 times as long per step).  36 x 3 spills a few and still is the
+// better: half the launches of 36 x 2 for problems of 2700 columns.
 struct PVariant {
   int T, C;
   const void* fn;
 };
+#define PV(T_, C_) {T_, C_, reinterpret_cast<const void*>(&qrcp_persist_kernel<T_, C_>)}
 static const PVariant kPVariants[] = {
-    {8, 8, reinterpret_cast<const void*>(&qrcp_persist_kernel<8, 8>)},
-    {12, 7, reinterpret_cast<const void*>(&qrcp_persist_kernel<12, 7>)},
-    {16, 6, reinterpret_cast<const void*>(&qrcp_persist_kernel<16, 6>)},
-    {24, 4, reinterpret_cast<const void*>(&qrcp_persist_kernel<24, 4>)},
-    {32, 3, reinterpret_cast<const void*>(&qrcp_persist_kernel<32, 3>)},
-    {36, 3, reinterpret_cast<const void*>(&qrcp_persist_kernel<36, 3>)},
-    {40, 2, reinterpret_cast<const void*>(&qrcp_persist_kernel<40, 2>)},
+    PV(4, 16), PV(4, 12), PV(4, 8), PV(4, 4), PV(4, 2),
+    PV(6, 12), PV(6, 10), PV(6, 8), PV(6, 6), PV(6, 4), PV(6, 2),
+    PV(8, 10), PV(8, 8), PV(8, 6), PV(8, 5), PV(8, 4), PV(8, 3), PV(8, 2),
+    PV(12, 7), PV(12, 6), PV(12, 5), PV(12, 4), PV(12, 3), PV(12, 2),
+    PV(16, 6), PV(16, 5), PV(16, 4), PV(16, 3), PV(16, 2),
+    PV(20, 4), PV(20, 3), PV(20, 2),
+    PV(24, 4), PV(24, 3), PV(24, 2),
+    PV(28, 3), PV(28, 2),
+    PV(32, 3), PV(32, 2), PV(32, 1),
+    PV(36, 3), PV(36, 2), PV(36, 1),
+    PV(40, 2), PV(40, 1),
 };
+#undef PV
+constexpr int kNumPVariants = sizeof(kPVariants) / sizeof(kPVariants[0]);
 
 // cost model constants (measured on gfx950): time per pivot step of a
-// persistent launch, a base plus a term that grows with the workgroups of its
-// widest problem (each one publishes a candidate every step: 7.5 us at 4,
-// 10.7 us at 167); the floor of one step-path launch, and the rate at which
-// the step path moves the active rows
-constexpr double kPersistStepUs = 7.3;
-constexpr double kPersistStepUsPerWg = 0.02;
+// persistent launch, a base and terms that grow with the values per lane
+// (T C) and with the workgroups of its widest problem, each of which
+// publishes a candidate every step (3.7 us at 32 values and 10 workgroups,
+// 4.3 at 64 and 5, 5.4 at 96 and 28, 7.0 at 96 and 116), and per launch; the
+// floor of one step-path launch, and the rate at which the step path moves
+// the active rows
+constexpr double kPersistLaunchUs = 20.0;
+constexpr double kPersistStepUs = 2.8;
+constexpr double kPersistStepUsPerValue = 0.022;
+constexpr double kPersistStepUsPerWg = 0.015;
 constexpr double kStepFloorUs = 25.0;
 constexpr double kStepBytesPerS = 3.0e12;
 
+static int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  return cus;
+}
 static int resident_workgroups(const void* fn) {
   int dev = 0, cus = 0, per = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
@@ -1534,32 +1618,31 @@ static hipError_t run_persistent(std::vector<DevProb>& h, const std::vector<int>
     rest.insert(rest.end(), cand.begin(), cand.end());
     return hipSuccess;
   }
-  int v = 0;
-  while (kPVariants[v].T * 64 < dmax) ++v;
-  const PVariant& pv = kPVariants[v];
-  const int cpg = PW * pv.C;
-  int maxwg = (int)std::min<long long>(resident_workgroups(pv.fn), w.nslots);
+  int wgcap = device_cus();  // one workgroup per compute unit
   if (const char* cap = std::getenv("HSS_QRCP_PERSIST_WG")) {  // tests: fewer workgroups per launch
     const int c = std::atoi(cap);
-    if (c > 0) maxwg = std::min(maxwg, c);
+    if (c > 0) wgcap = std::min(wgcap, c);
   }
-  if (!force_pers) {
-    // persistent: launches run one after another, each ~kPersistStepUs per
-    // step; step path: one launch per step for the whole batch, bound by
-    // the larger of the launch floor and the traffic (read + write of the
-    // active rows)
-    double t_pers = 0.0, bytes = 0.0;
-    int smax = 0, nwg = 0, lsteps = 0, lg = 0;
+  wgcap = (int)std::min<long long>(wgcap, w.nslots);
+  // time of the batch on a variant: its launches run one after another, each
+  // as many steps as its longest problem takes (problems too wide for a
+  // launch go to the step path)
+  auto persist_us = [&](const PVariant& pv, int cap) {
+    auto launch_us = [&](int steps, int g) {
+      return steps ? kPersistLaunchUs + steps * (kPersistStepUs + kPersistStepUsPerValue * pv.T * pv.C +
+                                                 kPersistStepUsPerWg * g)
+                   : 0.0;
+    };
+    double t = 0.0;
+    int nwg = 0, lsteps = 0, lg = 0;
     for (int q : cand) {
       const IdProblem& p = h[q].p;
       int steps = h[q].kmax;
       if (p.kfail >= 0 && p.m > p.d) steps = std::min(steps, p.kfail + 2);
-      smax = std::max(smax, steps);
-      bytes += 16.0 * p.m * std::max(1.0, p.d - 0.5 * steps);  // per step, averaged
-      const int G = (p.m + cpg - 1) / cpg;
-      if (G > maxwg) continue;
-      if (nwg + G > maxwg) {
-        t_pers += lsteps * (kPersistStepUs + kPersistStepUsPerWg * lg);
+      const int G = (p.m + PW * pv.C - 1) / (PW * pv.C);
+      if (G > cap) continue;
+      if (nwg + G > cap) {
+        t += launch_us(lsteps, lg);
         nwg = 0;
         lsteps = 0;
         lg = 0;
@@ -1568,7 +1651,40 @@ static hipError_t run_persistent(std::vector<DevProb>& h, const std::vector<int>
       lsteps = std::max(lsteps, steps);
       lg = std::max(lg, G);
     }
-    t_pers += lsteps * (kPersistStepUs + kPersistStepUsPerWg * lg);
+    return t + launch_us(lsteps, lg);
+  };
+  // The variant that takes the batch through in the least time: wide ones
+  // need fewer launches, narrow ones less arithmetic per step, and how the
+  // problems fill the device decides.  64 problems of 313 columns and 352
+  // rows: 8 columns per wavefront would be two launches (320 workgroups),
+  // 10 are one; two of 934 columns run 2 columns per wavefront.
+  int v = 0, mmax = 0;
+  while (kPVariants[v].T * 64 < dmax) ++v;
+  for (int q : cand) mmax = std::max(mmax, h[q].p.m);
+  double t_pers = persist_us(kPVariants[v], wgcap);
+  for (int v2 = v + 1; v2 < kNumPVariants && kPVariants[v2].T == kPVariants[v].T; ++v2) {
+    if ((mmax + PW * kPVariants[v2].C - 1) / (PW * kPVariants[v2].C) > wgcap) break;
+    const double t = persist_us(kPVariants[v2], wgcap);
+    if (t < t_pers) {
+      t_pers = t;
+      v = v2;
+    }
+  }
+  const PVariant& pv = kPVariants[v];
+  const int cpg = PW * pv.C;
+  const int maxwg = std::min(resident_workgroups(pv.fn), wgcap);
+  if (!force_pers) {
+    // step path: one launch per step for the whole batch, bound by the larger
+    // of the launch floor and the traffic (read + write of the active rows)
+    double bytes = 0.0;
+    int smax = 0;
+    for (int q : cand) {
+      const IdProblem& p = h[q].p;
+      int steps = h[q].kmax;
+      if (p.kfail >= 0 && p.m > p.d) steps = std::min(steps, p.kfail + 2);
+      smax = std::max(smax, steps);
+      bytes += 16.0 * p.m * std::max(1.0, p.d - 0.5 * steps);  // per step, averaged
+    }
     const double t_step = smax * std::max(kStepFloorUs, bytes * 1e6 / kStepBytesPerS);
     const char* vb = std::getenv("HSS_VERBOSE");
     if (vb && vb[0] >= '2') {

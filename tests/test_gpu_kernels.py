@@ -10,6 +10,8 @@ Tolerances (FP64, u = 2^-53):
   equal exactly; E = (R1^{-1} R2)^T agrees to 1e-10 relative (the QR
   factors differ by rounding, amplified by cond(R1)).
 """
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -257,6 +259,46 @@ def test_persistent_give_up_reruns_on_step_path(monkeypatch, capfd):
         assert abs(k - ref.k) <= 1
         if rate >= 0.3:
             assert k == ref.k and list(perm[:k]) == list(ref.J)
+
+
+@pytest.mark.parametrize("d,widest", [(250, 16), (384, 12), (500, 10), (760, 7), (1000, 6), (1270, 4),
+                                      (1500, 4), (1790, 3), (2040, 3), (2300, 3), (2500, 2)])
+def test_persistent_widths_agree(d, widest, monkeypatch, capfd):
+    """Every width (columns per wavefront) of a persistent variant gives the
+    same factorization, bit for bit: the width decides only which workgroup
+    holds a column.  The cap on workgroups per launch forces each width; the
+    ID reproduces Y to its tolerance, as above."""
+    m, rtol = 300, 1e-6
+    y = _slow_decay(d, m, d, 0.1)
+    Y = torch.from_numpy(np.ascontiguousarray(y.T)).cuda()
+    monkeypatch.setenv("HSS_QRCP_PATH", "persistent")
+    monkeypatch.setenv("HSS_VERBOSE", "2")
+    first, seen = None, set()
+    for cap in (3, 4, 5, 6, 7, 8, 10, 13, 19, 38):  # ceil(300 / (8 C)) for every C
+        monkeypatch.setenv("HSS_QRCP_PERSIST_WG", str(cap))
+        capfd.readouterr()
+        print(f"persistent widths: d={d}, at most {cap} workgroups", flush=True)
+        k, perm, E = P.hss_id_batched([Y], rtol)[0]
+        err = capfd.readouterr().err
+        assert "persistent wait gave up" not in err
+        got = re.findall(r"persistent launch: 1 problems, (\d+) workgroups", err)
+        if not got:  # fewer workgroups than the widest needs: the step path
+            assert cap < -(-m // (8 * widest))
+            continue
+        assert int(got[0]) <= cap
+        seen.add(int(got[0]))
+        if first is None:
+            first = (k, perm, E)
+        assert k == first[0] and np.array_equal(perm, first[1]) and np.array_equal(E, first[2])
+    assert len(seen) >= 2
+    k, perm, E = first
+    ref = interp.interpolative_decomposition(y, rtol)
+    assert abs(k - ref.k) <= 1
+    X = np.zeros((k, m))
+    X[:, perm[:k]] = np.eye(k)
+    X[:, perm[k:]] = E.T
+    res = np.linalg.norm(y - y[:, perm[:k]] @ X, 2)
+    assert res <= 10 * np.sqrt(max(1, m - k)) * rtol * np.linalg.norm(y, axis=0).max()
 
 
 @pytest.mark.parametrize("variant", list(range(-1, 7)))
