@@ -291,13 +291,9 @@ __device__ __forceinline__ void group_argmax(double& bv, int& bi) {
   if (P > 4) better(bv, bi, dpp_d<0x141>(bv), dpp_i<0x141>(bi));
   if (P > 8) better(bv, bi, dpp_d<0x140>(bv), dpp_i<0x140>(bi));
 }
-// the best pair of lanes 0..n-1 in lane 0 (in every lane for n > 16); n uniform
-__device__ __forceinline__ void first_argmax(double& bv, int& bi, int n) {
-  group_argmax<8>(bv, bi);
-  if (n <= 8) return;
-  better(bv, bi, dpp_d<0x140>(bv), dpp_i<0x140>(bi));
-  if (n <= 16) return;
-  // across rows: the better of {own, partner} in either order (a total order)
+// across the four rows of 16 lanes: the better of {own, partner} in either
+// order (a total order)
+__device__ __forceinline__ void rows_argmax(double& bv, int& bi) {
   double av, cv;
   int ai, ci;
   cross_pair<16>(bv, av, cv);
@@ -309,10 +305,21 @@ __device__ __forceinline__ void first_argmax(double& bv, int& bi, int n) {
   bv = av, bi = ai;
   better(bv, bi, cv, ci);
 }
+// the best pair of lanes 0..n-1 in lane 0 (in every lane for n > 16); n uniform
+__device__ __forceinline__ void first_argmax(double& bv, int& bi, int n) {
+  group_argmax<8>(bv, bi);
+  if (n <= 8) return;
+  better(bv, bi, dpp_d<0x140>(bv), dpp_i<0x140>(bi));
+  if (n > 16) rows_argmax(bv, bi);
+}
 
 // ---------------------------------------------------------------------------
 // small problems: one workgroup, matrix in registers
 // ---------------------------------------------------------------------------
+// A step is bound by the instructions of the columns' sums, taken eight
+// columns at a time and spread over lanes (64 instructions where eight
+// butterflies are 176), and by its two barriers.  32 problems of 256 columns,
+// IDs and all: 128 rows 2.91 -> 2.51 ms, 192 rows 3.40 -> 2.97 ms.
 // NOPIV: every problem of the launch factors without pivoting (step i's
 // pivot is column i).  Then no candidate is searched and no norm kept but
 // the pivot column's own, which its wavefront forms from its registers (in
@@ -324,6 +331,7 @@ __global__ __launch_bounds__(RW * 64) void qrcp_reg_kernel(const DevProb* __rest
                                                           Work w) {
   __shared__ double xcol[NOPIV ? 2 : 1][RPL * 64];
   __shared__ double pn_s[2];
+  constexpr int SB = 8;  // columns whose sums are taken together (registers)
   __shared__ double nrm_s[RW * CPW];  // squared norms: compared as they are, the winner's root taken
   __shared__ int step_s[RW * CPW];
   __shared__ double red_v[RW];
@@ -335,23 +343,37 @@ __global__ __launch_bounds__(RW * 64) void qrcp_reg_kernel(const DevProb* __rest
   const int m = P.m, d = P.d;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
+  // a lane's share of the SB columns c0.. whose sums are taken together:
+  // column c0 + sc, norm and liveness
+  const int sc = lane & (SB - 1);
+  double bv = -1.0;  // this wavefront's best candidate of the step to come
+  int bi = INT_MAX;
+  unsigned sel = 0;  // columns of this wavefront already chosen as pivots
   double y[CPW][RPL];
 #pragma unroll
-  for (int c = 0; c < CPW; ++c) {
-    const int j = wave + RW * c;
-    double s = 0.0;
+  for (int c0 = 0; c0 < CPW; c0 += SB) {
+    double s[SB];
 #pragma unroll
-    for (int t = 0; t < RPL; ++t) {
-      const int r = lane + 64 * t;
-      const double v = (j < m && r < d) ? P.Y[(long long)j * P.ldy + r] : 0.0;
-      y[c][t] = v;
-      s = fma(v, v, s);
+    for (int cc = 0; cc < SB; ++cc) {
+      const int j = wave + RW * (c0 + cc);
+      s[cc] = 0.0;
+#pragma unroll
+      for (int t = 0; t < RPL; ++t) {
+        const int r = lane + 64 * t;
+        const double v = (j < m && r < d) ? P.Y[(long long)j * P.ldy + r] : 0.0;
+        y[c0 + cc][t] = v;
+        s[cc] = fma(v, v, s[cc]);
+      }
     }
-    if constexpr (!NOPIV) s = wave_sum(s);
-    if (lane == 0 && j < m) {
-      if constexpr (!NOPIV) nrm_s[j] = s;
-      step_s[j] = -1;
+    const int j = wave + RW * (c0 + sc);
+    if constexpr (!NOPIV) {
+      const double q2 = wave_sums_spread<SB>(s, lane);
+      if (j < m) {
+        better(bv, bi, q2, j);
+        if (lane < SB) nrm_s[j] = q2;
+      }
     }
+    if (lane < SB && j < m) step_s[j] = -1;
   }
   __syncthreads();
   const int kmax = dp.kmax;
@@ -398,15 +420,24 @@ __global__ __launch_bounds__(RW * 64) void qrcp_reg_kernel(const DevProb* __rest
       }
       // the columns after the pivot (the earlier ones are finished)
 #pragma unroll
-      for (int c = 0; c < CPW; ++c) {
-        const int j = wave + RW * c;
-        if (j >= m || j <= i) continue;
-        double dot = 0.0;
+      for (int c0 = 0; c0 < CPW; c0 += SB) {
+        if (wave + RW * (c0 + SB - 1) <= i || wave + RW * c0 >= m) continue;
+        double f[SB];
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) dot = fma(uu[t], y[c][t], dot);
-        const double f = tau * wave_sum(dot);
+        for (int cc = 0; cc < SB; ++cc) {
+          f[cc] = 0.0;
 #pragma unroll
-        for (int t = 0; t < RPL; ++t) y[c][t] = fma(-f, uu[t], y[c][t]);
+          for (int t = 0; t < RPL; ++t) f[cc] = fma(uu[t], y[c0 + cc][t], f[cc]);
+        }
+        const int j = wave + RW * (c0 + sc);
+        const double fr = tau * wave_sums_spread<SB>(f, lane);
+        const double fl = (j < m && j > i) ? fr : 0.0;
+#pragma unroll
+        for (int cc = 0; cc < SB; ++cc) {
+          const double fc = lane_value(fl, cc);
+#pragma unroll
+          for (int t = 0; t < RPL; ++t) y[c0 + cc][t] = fma(-fc, uu[t], y[c0 + cc][t]);
+        }
       }
       k = i + 1;
       // no closing barrier: the next step writes the other buffer, and the
@@ -415,22 +446,18 @@ __global__ __launch_bounds__(RW * 64) void qrcp_reg_kernel(const DevProb* __rest
     }
   } else {
   for (int i = 0; i < kmax; ++i) {
-    double bv = -1.0;
-    int bi = INT_MAX;
-    for (int j = tid; j < m; j += RW * 64)
-      if (step_s[j] < 0) better(bv, bi, nrm_s[j], j);
-    wave_argmax(bv, bi);
+    group_argmax<SB>(bv, bi);
     if (lane == 0) {
       red_v[wave] = bv;
       red_i[wave] = bi;
     }
     __syncthreads();
-    // every thread reduces the RW wavefront results (no second barrier);
-    // red_v / red_i are written again only after this step's later barriers
-    double sb = red_v[0];
-    int sp = red_i[0];
-#pragma unroll
-    for (int q2 = 1; q2 < RW; ++q2) better(sb, sp, red_v[q2], red_i[q2]);
+    // every wavefront reduces the RW results (no second barrier); red_v /
+    // red_i are written again only after this step's later barrier
+    double sb = red_v[lane & (RW - 1)];
+    int sp = red_i[lane & (RW - 1)];
+    group_argmax<RW>(sb, sp);
+    sp = __builtin_amdgcn_readfirstlane(sp);
     const bool nopiv = P.nfac > 0;
     const double best = sqrt(fmax(nopiv ? nrm_s[i] : sb, 0.0));  // -1 (no candidate) stops as 0 would
     const int p = nopiv ? i : sp;
@@ -445,6 +472,7 @@ __global__ __launch_bounds__(RW * 64) void qrcp_reg_kernel(const DevProb* __rest
 #pragma unroll
           for (int t = 0; t < RPL; ++t) xcol[0][lane + 64 * t] = y[c][t];
         }
+      sel |= 1u << cp;
     }
     if (tid == 0) step_s[p] = i;
     __syncthreads();
@@ -473,27 +501,46 @@ __global__ __launch_bounds__(RW * 64) void qrcp_reg_kernel(const DevProb* __rest
       w.alpha[dp.aoff + i] = alpha;
       w.piv[dp.aoff + i] = p;
     }
+    // H applied to the live columns, SB columns' sums at a time; their new
+    // norms become the next step's candidates
+    bv = -1.0;
+    bi = INT_MAX;
 #pragma unroll
-    for (int c = 0; c < CPW; ++c) {
-      const int j = wave + RW * c;
-      if (j >= m || step_s[j] >= 0) continue;
-      double dot = 0.0;
+    for (int c0 = 0; c0 < CPW; c0 += SB) {
+      if (((sel >> c0) & ((1u << SB) - 1)) == (1u << SB) - 1 || wave + RW * c0 >= m) continue;
+      double f[SB];
 #pragma unroll
-      for (int t = 0; t < RPL; ++t) dot = fma(uu[t], y[c][t], dot);
-      const double f = tau * wave_sum(dot);
-      double s = 0.0;
+      for (int cc = 0; cc < SB; ++cc) {
+        f[cc] = 0.0;
 #pragma unroll
-      for (int t = 0; t < RPL; ++t) {
-        const int r = lane + 64 * t;
-        const double v = fma(-f, uu[t], y[c][t]);
-        y[c][t] = v;
-        if (r > i && r < d) s = fma(v, v, s);
+        for (int t = 0; t < RPL; ++t) f[cc] = fma(uu[t], y[c0 + cc][t], f[cc]);
       }
-      s = wave_sum(s);
-      if (lane == 0) nrm_s[j] = s;
+      const int j = wave + RW * (c0 + sc);
+      const bool live = j < m && !((sel >> (c0 + sc)) & 1u);
+      const double fr = tau * wave_sums_spread<SB>(f, lane);
+      const double fl = live ? fr : 0.0;
+      double s[SB];
+#pragma unroll
+      for (int cc = 0; cc < SB; ++cc) {
+        const double fc = lane_value(fl, cc);
+        s[cc] = 0.0;
+#pragma unroll
+        for (int t = 0; t < RPL; ++t) {
+          const int r = lane + 64 * t;
+          const double v = fma(-fc, uu[t], y[c0 + cc][t]);
+          y[c0 + cc][t] = v;
+          if (r > i && r < d) s[cc] = fma(v, v, s[cc]);
+        }
+      }
+      const double q2 = wave_sums_spread<SB>(s, lane);
+      if (live) {
+        better(bv, bi, q2, j);
+        if (lane < SB) nrm_s[j] = q2;
+      }
     }
     k = i + 1;
-    __syncthreads();
+    // no closing barrier: xcol, red_v and nrm_s are written next only after
+    // the next step's first barrier (nrm_s: read before this step's second)
   }
   }
   __syncthreads();  // step_s complete before the write-back
@@ -663,17 +710,16 @@ __global__ __launch_bounds__(512) void qrcp_reg16_kernel(const DevProb* __restri
   } else {
   for (int i = 0; i < kmax; ++i) {
     // candidates across the four rows of the wavefront, then across wavefronts
-    better(bv, bi, __shfl_xor(bv, 16, 64), __shfl_xor(bi, 16, 64));
-    better(bv, bi, __shfl_xor(bv, 32, 64), __shfl_xor(bi, 32, 64));
+    rows_argmax(bv, bi);
     if (lane == 0) {
       red_v[wave] = bv;
       red_i[wave] = bi;
     }
     __syncthreads();
-    double sb = red_v[0];
-    int sp = red_i[0];
-#pragma unroll
-    for (int w2 = 1; w2 < RW; ++w2) better(sb, sp, red_v[w2], red_i[w2]);
+    double sb = red_v[lane & (RW - 1)];
+    int sp = red_i[lane & (RW - 1)];
+    group_argmax<RW>(sb, sp);
+    sp = __builtin_amdgcn_readfirstlane(sp);
     const double best = sqrt(fmax(nopiv ? nrm_s[i] : sb, 0.0));  // -1 (no candidate) stops as 0 would
     const int p = nopiv ? i : sp;
     if (i == 0) nu0 = best;
@@ -1877,11 +1923,11 @@ static int small_resident(int c) {
         reinterpret_cast<const void*>(&qrcp_reg16_kernel<8, 4>),
         reinterpret_cast<const void*>(&qrcp_reg16_kernel<2, 8>),
         reinterpret_cast<const void*>(&qrcp_reg16_kernel<4, 8>),
-        reinterpret_cast<const void*>(&qrcp_reg_kernel<16, 16, 2>),
+        reinterpret_cast<const void*>(&qrcp_reg_kernel<8, 32, 2>),
         reinterpret_cast<const void*>(&qrcp_reg16_kernel<2, 12>),
         reinterpret_cast<const void*>(&qrcp_reg16_kernel<4, 12>),
-        reinterpret_cast<const void*>(&qrcp_reg_kernel<16, 16, 3>)};
-    const int waves[kSmallClasses] = {8, 8, 8, 8, 8, 8, 16, 8, 8, 16};
+        reinterpret_cast<const void*>(&qrcp_reg_kernel<8, 32, 3>)};
+    const int waves[kSmallClasses] = {8, 8, 8, 8, 8, 8, 8, 8, 8, 8};
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -2015,8 +2061,9 @@ hipError_t launch_id_factor(IdProblem* probs, int nprob, double rtol, void* work
       // 16 lanes per column: (column groups, rows per lane) = 32 G columns,
       // 16 R rows; the two largest classes, whose 16-lane form would spill
       // registers inside the step loop, keep 64 lanes per column (W
-      // wavefronts, C columns per wavefront, R rows per lane), on 16
-      // wavefronts: each runs half as many columns' sum chains per step
+      // wavefronts, C columns per wavefront, R rows per lane), on 8
+      // wavefronts with 256 registers a lane (on 16 with 128 the sums of
+      // eight columns at a time spill)
       switch (c) {
         case 0: QR_LAUNCH(1, 4); break;
         case 1: QR_LAUNCH(2, 4); break;
@@ -2024,10 +2071,10 @@ hipError_t launch_id_factor(IdProblem* probs, int nprob, double rtol, void* work
         case 3: QR_LAUNCH(8, 4); break;
         case 4: QR_LAUNCH(2, 8); break;
         case 5: QR_LAUNCH(4, 8); break;
-        case 6: QR_LAUNCH64(16, 16, 2); break;
+        case 6: QR_LAUNCH64(8, 32, 2); break;
         case 7: QR_LAUNCH(2, 12); break;
         case 8: QR_LAUNCH(4, 12); break;
-        default: QR_LAUNCH64(16, 16, 3); break;
+        default: QR_LAUNCH64(8, 32, 3); break;
       }
 #undef QR_LAUNCH
 #undef QR_LAUNCH64

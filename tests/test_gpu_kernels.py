@@ -261,6 +261,23 @@ def test_persistent_give_up_reruns_on_step_path(monkeypatch, capfd):
             assert k == ref.k and list(perm[:k]) == list(ref.J)
 
 
+@pytest.mark.parametrize("d,m", [(65, 129), (128, 256), (127, 255), (129, 129), (192, 256), (130, 161)])
+def test_id_largest_register_classes(d, m):
+    """The one-workgroup classes that hold a column in 64 lanes, at the edges
+    of their rows and columns: the oracle's pivots where the norms are well
+    separated, and the lowest index at exact ties (every column twice)."""
+    y = _slow_decay(d, m, d + m, 0.37)
+    twice = 2.0 * np.eye(d)[:, np.arange(m) % d]
+    got = P.hss_id_batched([torch.from_numpy(np.ascontiguousarray(a.T)).cuda() for a in (y, twice)], 1e-6)
+    k, perm, E = got[0]
+    ref = interp.interpolative_decomposition(y, 1e-6)
+    assert k == ref.k and list(perm[:k]) == list(ref.J)
+    assert np.allclose(E, ref.E, rtol=1e-8, atol=1e-8 * max(1.0, np.abs(ref.E).max()))
+    k, perm, E = got[1]
+    assert k == d and list(perm[:k]) == list(range(d)) and list(perm[k:]) == list(range(d, m))
+    assert np.array_equal(E, np.eye(d)[np.arange(d, m) % d])
+
+
 @pytest.mark.parametrize("d,widest", [(250, 16), (384, 12), (500, 10), (760, 7), (1000, 6), (1270, 4),
                                       (1500, 4), (1790, 3), (2040, 3), (2300, 3), (2500, 2)])
 def test_persistent_widths_agree(d, widest, monkeypatch, capfd):
