@@ -1476,7 +1476,7 @@ __global__ __launch_bounds__(NT) void id_perm_kernel(const DevProb* __restrict__
 }
 
 // Diagonal block of the solve E * Rt = R2^T with Rt = R1^T lower
-// triangular: for every unselected column c (one thread each),
+// triangular: for every unselected column c,
 // x[a] = (y[a] - sum_{b > a} x[b] Rt[b][a]) / Rt[a][a] on [b0, b1).
 struct DiagDesc {
   const double* W;
@@ -1484,52 +1484,107 @@ struct DiagDesc {
   const int* perm;
   double* E;
   int k, nrest, b0, b1;
-  long long wg0;
 };
+typedef __attribute__((address_space(1))) double gdouble;
+typedef __attribute__((address_space(1))) const int gint_c;
+__device__ __forceinline__ gdouble* as_global(const double* p) { return (gdouble*)(uintptr_t)p; }
 
-// NB: 64, or 32 / 16 when every block of the launch has at most that many
-// rows (low ranks): the padded steps add signed zeros only, so the result is
-// the same with fewer steps and registers.
-template <int NB>
-__global__ __launch_bounds__(NT) void trsm_diag_kernel(const DiagDesc* __restrict__ descs, int nd) {
-  __shared__ double Rt[NB][NB + 1];
-  int lo = 0, hi = nd - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (descs[mid].wg0 <= (long long)blockIdx.x) lo = mid;
-    else hi = mid - 1;
+// A wavefront solves TC columns at once, lane a holding x[a]: row b of Rt is
+// applied once x[b] is final, read from its lane by all others.  Entries at
+// and past b meet a zero of Rt, so the fast form needs no select; the plain
+// one (a diagonal outside 2^+-500, or a result that is not finite) divides
+// in place and leaves the entries past b alone.
+constexpr int TC = 8, TW = 4;  // columns per wavefront, wavefronts
+template <bool PLAIN>
+__device__ __forceinline__ void trsm_diag_solve(double (&x)[TC], const double (*Rt)[64], int nb, double d, double r) {
+  const int lane = threadIdx.x & 63;
+  auto quot = [&](double v) {
+    if (PLAIN) return v / d;
+    const double q = v * r;  // correctly rounded reciprocal: one Newton step gives the quotient
+    return fma(fma(-q, d, v), r, q);
+  };
+  constexpr int U = 4;  // rows read ahead
+  for (int b0 = nb - 1; b0 > 0; b0 -= U) {
+    double t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = Rt[max(b0 - u, 0)][lane];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = b0 - u;
+      if (b <= 0) break;
+#pragma unroll
+      for (int c = 0; c < TC; ++c) {
+        const double xb = lane_value(quot(x[c]), b);
+        const double v = fma(-xb, t[u], x[c]);
+        x[c] = PLAIN && lane >= b ? x[c] : v;
+      }
+    }
   }
-  const DiagDesc g = descs[lo];
-  const int nb = g.b1 - g.b0;
-  // padded to NB x NB with the identity: the padded entries solve to zero
-  // and the unrolled loops below need no test against nb
-  for (int e = threadIdx.x; e < NB * NB; e += NT) {
-    const int bb = e / NB, aa = e % NB;
-    Rt[bb][aa] = (bb < nb && aa <= bb)
-                     ? g.W[(long long)g.perm[g.b0 + bb] * g.ldw + g.b0 + aa]
-                     : (aa == bb ? 1.0 : 0.0);
+#pragma unroll
+  for (int c = 0; c < TC; ++c) x[c] = quot(x[c]);
+}
+
+// blockIdx.x the block, grid y strides its columns.  What bounds it: the
+// chain of nb steps, each a quotient, a broadcast and a fused step.  With a
+// thread per column and the 64 steps unrolled (58 us per launch, whatever
+// the width) it was the fetch of 2000 instructions that run once, behind a
+// search for the descriptor, rows of R1 loaded four at a time behind their
+// permutation entries, and x strided by k across lanes; here the loop is
+// short, every row of R1 and of E is one contiguous load, all in flight.
+// 64-row blocks take 13 us per launch.
+__global__ __launch_bounds__(TW * 64) void trsm_diag_kernel(const DiagDesc* __restrict__ descs) {
+  __shared__ double Rt[64][64];
+  const DiagDesc g = descs[blockIdx.x];
+  const int nb = g.b1 - g.b0, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)blockIdx.y * TC * TW >= g.nrest) return;
+  const int al = min(lane, nb - 1);
+  gdouble* e0 = as_global(g.E) + g.b0 + al;
+  int c0 = ((int)blockIdx.y * TW + wave) * TC;
+  double x[TC];
+  auto load_x = [&]() {
+#pragma unroll
+    for (int c = 0; c < TC; ++c) x[c] = e0[(long long)min(c0 + c, g.nrest - 1) * g.k];
+  };
+  load_x();
+  const int pl = ((gint_c*)(uintptr_t)g.perm)[g.b0 + al];
+  constexpr int NR = 64 / TW;
+  double v[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int b = wave + TW * q;
+    const long long pj = __builtin_amdgcn_readlane(pl, b);
+    v[q] = as_global(g.W)[pj * g.ldw + g.b0 + min(al, b)];
+  }
+  double d = 1.0;
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int b = wave + TW * q;
+    Rt[b][lane] = lane <= b ? v[q] : 0.0;
   }
   __syncthreads();
-  const int c = (int)(blockIdx.x - g.wg0) * NT + threadIdx.x;
-  if (c >= g.nrest) return;
-  double* x = g.E + (long long)c * g.k + g.b0;
-  double xv[NB];
+  if (lane < nb) d = Rt[lane][lane];
+  __syncthreads();
+  if (lane % TW == wave) Rt[lane][lane] = 0.0;
+  __syncthreads();
+  const double r = 1.0 / d;
+  const bool plain = __any(!(fabs(d) > 0x1p-500 && fabs(d) < 0x1p500));
+  while (c0 < g.nrest) {
+    bool again = plain;
+    if (!again) {
+      trsm_diag_solve<false>(x, Rt, nb, d, r);
+      bool fin = true;
 #pragma unroll
-  for (int a = 0; a < NB; ++a) {  // entries past nb read entry 0 and are zeroed
-    const double v = x[a < nb ? a : 0];
-    xv[a] = a < nb ? v : 0.0;
+      for (int c = 0; c < TC; ++c) fin = fin && fabs(x[c]) <= 1.7976931348623157e308;
+      again = __any(!fin);
+      if (again) load_x();
+    }
+    if (again) trsm_diag_solve<true>(x, Rt, nb, d, r);
+#pragma unroll
+    for (int c = 0; c < TC; ++c)
+      if (lane < nb && c0 + c < g.nrest) e0[(long long)(c0 + c) * g.k] = x[c];
+    c0 += (int)gridDim.y * TC * TW;
+    if (c0 < g.nrest) load_x();
   }
-  // column by column, from the last: once x[b] is final, the updates of the
-  // entries above it are independent of each other
-#pragma unroll
-  for (int b = NB - 1; b >= 0; --b) {
-    xv[b] = xv[b] / Rt[b][b];
-#pragma unroll
-    for (int a = 0; a < b; ++a) xv[a] = fma(-xv[b], Rt[b][a], xv[a]);
-  }
-#pragma unroll
-  for (int a = 0; a < NB; ++a)
-    if (a < nb) x[a] = xv[a];
 }
 
 }  // namespace
@@ -2212,7 +2267,7 @@ hipError_t launch_id_finish(const IdProblem* probs, int nprob, const int* k_host
   for (int b = maxblk - 1; b >= 0; --b) {
     gd.clear();
     dd.clear();
-    long long wg = 0;
+    int cblk = 0;  // blocks of the widest problem's columns
     for (int t = 0; t < nsel; ++t) {
       const int q = sel[t], k = k_host[q];
       const IdProblem& p = probs[q];
@@ -2240,8 +2295,7 @@ hipError_t launch_id_finish(const IdProblem* probs, int nprob, const int* k_host
       x.nrest = nrest;
       x.b0 = b0;
       x.b1 = b1;
-      x.wg0 = wg;
-      wg += (nrest + NT - 1) / NT;
+      cblk = std::max(cblk, (nrest + TC * TW - 1) / (TC * TW));
       dd.push_back(x);
     }
     if (dd.empty()) continue;
@@ -2249,14 +2303,8 @@ hipError_t launch_id_finish(const IdProblem* probs, int nprob, const int* k_host
     if (e != hipSuccess) return e;
     const DiagDesc* ddev = static_cast<const DiagDesc*>(st.push(dd.data(), dd.size() * sizeof(DiagDesc)));
     if (!ddev) return hipErrorOutOfMemory;
-    int nbmax = 1;
-    for (const DiagDesc& x : dd) nbmax = std::max(nbmax, x.b1 - x.b0);
-    if (nbmax <= 16)
-      hipLaunchKernelGGL(trsm_diag_kernel<16>, dim3((unsigned)wg), dim3(NT), 0, s, ddev, (int)dd.size());
-    else if (nbmax <= 32)
-      hipLaunchKernelGGL(trsm_diag_kernel<32>, dim3((unsigned)wg), dim3(NT), 0, s, ddev, (int)dd.size());
-    else
-      hipLaunchKernelGGL(trsm_diag_kernel<64>, dim3((unsigned)wg), dim3(NT), 0, s, ddev, (int)dd.size());
+    const dim3 grid((unsigned)dd.size(), (unsigned)std::min(cblk, 65535));
+    hipLaunchKernelGGL(trsm_diag_kernel, grid, dim3(TW * 64), 0, s, ddev);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -278,6 +278,22 @@ def test_id_largest_register_classes(d, m):
     assert np.array_equal(E, np.eye(d)[np.arange(d, m) % d])
 
 
+@pytest.mark.parametrize("k,nrest", [(1, 1), (2, 33), (63, 31), (64, 32), (65, 9), (129, 100)])
+def test_id_block_solve_edges(k, nrest):
+    """E = (R1^{-1} R2)^T at the edges of the solve's 64-row blocks and of its
+    column groups, against a dense solve with the chosen columns (full rank,
+    condition below 1e4: 1e-10 relative), and the same entries bit for bit
+    when every norm is scaled by 2^505, where the plain division runs."""
+    y = _slow_decay(k, k + nrest, 7 * k + nrest, 0.02)
+    one, big = P.hss_id_batched([torch.from_numpy(np.ascontiguousarray(y.T) * f).cuda() for f in (1.0, 2.0 ** 505)],
+                                1e-14)
+    assert one[0] == k
+    J, rest = one[1][:k], one[1][k:]
+    ref = np.linalg.solve(y[:, J], y[:, rest]).T
+    assert np.linalg.norm(one[2] - ref) <= 1e-10 * np.linalg.norm(ref)
+    assert big[0] == k and np.array_equal(big[1], one[1]) and np.array_equal(big[2], one[2])
+
+
 @pytest.mark.parametrize("d,widest", [(250, 16), (384, 12), (500, 10), (760, 7), (1000, 6), (1270, 4),
                                       (1500, 4), (1790, 3), (2040, 3), (2300, 3), (2500, 2)])
 def test_persistent_widths_agree(d, widest, monkeypatch, capfd):
