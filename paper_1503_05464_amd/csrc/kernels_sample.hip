@@ -29,6 +29,7 @@ namespace {
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));  // 16 bytes from any entry of A
 
 constexpr int BM = 128;
 constexpr int BN = 64;
@@ -52,76 +53,90 @@ __device__ __forceinline__ double widen(TA v) {
   return (double)v;
 }
 
-// Loads this thread's share (64 bytes) of the A slice into registers.
-// NN: A[i0 + r][k0 + kseg + e]; TN: A[k0 + kk][i0 + cseg + e].
+// This thread's share of the A slice: 4 pieces of 16 bytes, piece q holding
+// the entries (row, col ..) of the slice.  FP64, NN (A[i][k]): row tid / 8 +
+// 32 q, so that eight consecutive lanes read one row's 128 bytes in one
+// instruction.  FP32, NN: 64 bytes of one row (with eight lanes per row the
+// stores to LDS collide: 2.9 against 2.05 ms at n = 32768).  TN (A[k][i]): 64
+// bytes of row kk.  The loads need only the alignment of an entry, and go
+// through the caches (streamed past them, the four loads of a lane's 64
+// bytes fetched their lines more than once).  64 columns, ms, before ->
+// now: FP64 n = 20011 NN 1.78 -> 1.24, TN 1.18 -> 1.09; n = 32768 NN 2.71 ->
+// 2.45, TN 2.55 -> 2.34; FP32 n = 20011 NN 1.56 -> 1.05, TN 1.16 -> 1.05;
+// n = 32768 NN 2.13 -> 2.04, TN 2.10 -> 2.05.
+template <typename TA, bool TRANS>
+__device__ __forceinline__ void a_piece(int q, int& row, int& col) {
+  constexpr int E = 64 / sizeof(TA), EV = 16 / sizeof(TA);
+  constexpr int BK = Cfg<TA>::BK;
+  const int tid = threadIdx.x;
+  if (TRANS) {
+    row = tid / (BM / E);
+    col = (tid % (BM / E)) * E + q * EV;
+  } else if (sizeof(TA) == 8) {
+    row = (tid >> 3) + 32 * q;
+    col = (tid & 7) * EV;
+  } else {
+    row = tid / (BK / E);
+    col = (tid % (BK / E)) * E + q * EV;
+  }
+}
+
 template <typename TA, bool TRANS>
 __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __restrict__ A,
                                        long long lda, int n, int i0, int k0, int kend,
-                                       const int* __restrict__ leaf_of, bool vec_ok,
-                                       bool need_mask) {
-  constexpr int E = 64 / sizeof(TA);
-  constexpr int BK = Cfg<TA>::BK;
-  const int tid = threadIdx.x;
-  int row, col;  // indices into A
-  int ie, ke;    // (i, k) of element 0; element e adds to k (NN) or i (TN)
-  if (!TRANS) {
-    const int r = tid / (BK / E);
-    const int kseg = (tid % (BK / E)) * E;
-    row = i0 + r;
-    col = k0 + kseg;
-    ie = row;
-    ke = col;
-  } else {
-    const int kk = tid / (BM / E);
-    const int cseg = (tid % (BM / E)) * E;
-    row = k0 + kk;
-    col = i0 + cseg;
-    ie = col;
-    ke = row;
-  }
-  const bool full = !TRANS ? (row < n && col + E <= kend) : (row < kend && col + E <= n);
-  if (full && vec_ok) {
-    const u32x4* p = reinterpret_cast<const u32x4*>(A + (long long)row * lda + col);
+                                       const int* __restrict__ leaf_of, bool need_mask) {
+  constexpr int EV = 16 / sizeof(TA);
+  const int rbeg = !TRANS ? i0 : k0, cbeg = !TRANS ? k0 : i0;
+  if (i0 + BM <= n && k0 + Cfg<TA>::BK <= kend) {  // the whole slice is there
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      u32x4 w = __builtin_nontemporal_load(p + q);
+      int row, col;
+      a_piece<TA, TRANS>(q, row, col);
+      const u32x4_a4* p = reinterpret_cast<const u32x4_a4*>(A + (long long)(rbeg + row) * lda + cbeg + col);
+      u32x4 w = *p;
       TA* t = reinterpret_cast<TA*>(&w);
 #pragma unroll
-      for (int e = 0; e < (int)(16 / sizeof(TA)); ++e) v[q * (16 / sizeof(TA)) + e] = t[e];
+      for (int e = 0; e < EV; ++e) v[q * EV + e] = t[e];
     }
   } else {
+    const int rend = !TRANS ? n : kend, cend = !TRANS ? kend : n;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const bool ok = !TRANS ? (row < n && col + e < kend) : (row < kend && col + e < n);
-      v[e] = ok ? A[(long long)row * lda + col + e] : (TA)0;
+    for (int q = 0; q < 4; ++q) {
+      int row, col;
+      a_piece<TA, TRANS>(q, row, col);
+#pragma unroll
+      for (int e = 0; e < EV; ++e)
+        v[q * EV + e] = (rbeg + row < rend && cbeg + col + e < cend)
+                            ? A[(long long)(rbeg + row) * lda + cbeg + col + e]
+                            : (TA)0;
     }
   }
   if (need_mask) {
     // zero the entries of the leaf diagonal blocks: leaf_of[i] == leaf_of[k]
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int i = !TRANS ? ie : ie + e;
-      const int k = !TRANS ? ke + e : ke;
-      if (i < n && k < n && leaf_of[i] == leaf_of[k]) v[e] = (TA)0;
+    for (int q = 0; q < 4; ++q) {
+      int row, col;
+      a_piece<TA, TRANS>(q, row, col);
+#pragma unroll
+      for (int e = 0; e < EV; ++e)
+        if (rbeg + row < n && cbeg + col + e < n && leaf_of[rbeg + row] == leaf_of[cbeg + col + e])
+          v[q * EV + e] = (TA)0;
     }
   }
 }
 
 template <typename TA, bool TRANS>
 __device__ __forceinline__ void store_a(TA (*As)[BM + Cfg<TA>::PAD], const TA (&v)[64 / sizeof(TA)]) {
-  constexpr int E = 64 / sizeof(TA);
-  constexpr int BK = Cfg<TA>::BK;
-  const int tid = threadIdx.x;
-  if (!TRANS) {
-    const int r = tid / (BK / E);
-    const int kseg = (tid % (BK / E)) * E;
+  constexpr int EV = 16 / sizeof(TA);
 #pragma unroll
-    for (int e = 0; e < E; ++e) As[kseg + e][r] = v[e];
-  } else {
-    const int kk = tid / (BM / E);
-    const int cseg = (tid % (BM / E)) * E;
+  for (int q = 0; q < 4; ++q) {
+    int row, col;
+    a_piece<TA, TRANS>(q, row, col);
 #pragma unroll
-    for (int e = 0; e < E; ++e) As[kk][cseg + e] = v[e];
+    for (int e = 0; e < EV; ++e) {
+      if (TRANS) As[row][col + e] = v[q * EV + e];
+      else As[col + e][row] = v[q * EV + e];
+    }
   }
 }
 
@@ -188,8 +203,6 @@ __global__ __launch_bounds__(NT) void sample_kernel(
   const int wm = wave >> 1;
   const int wn = wave & 1;
 
-  const bool vec_a = ((lda * (long long)sizeof(TA)) % 16 == 0) &&
-                     ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
   const bool vec_r = (ldr % 2 == 0) && ((reinterpret_cast<uintptr_t>(R) & 15) == 0);
 
   // Does the leaf mask touch rows [i0, i0+BM) x k-range [k0, k0+BK)?
@@ -218,7 +231,7 @@ __global__ __launch_bounds__(NT) void sample_kernel(
 
   int k0 = kbeg;
   if (k0 < kend) {
-    load_a<TA, TRANS>(va, A, lda, n, i0, k0, kend, leaf_of, vec_a, mask_for(k0));
+    load_a<TA, TRANS>(va, A, lda, n, i0, k0, kend, leaf_of, mask_for(k0));
     load_r<BK>(vr, R, ldr, k0, kend, c0, ncols, vec_r);
     store_a<TA, TRANS>(As, va);
     store_r<BK>(Bs, vr);
@@ -227,7 +240,7 @@ __global__ __launch_bounds__(NT) void sample_kernel(
   for (; k0 < kend; k0 += BK) {
     const int kn = k0 + BK;
     if (kn < kend) {
-      load_a<TA, TRANS>(va, A, lda, n, i0, kn, kend, leaf_of, vec_a, mask_for(kn));
+      load_a<TA, TRANS>(va, A, lda, n, i0, kn, kend, leaf_of, mask_for(kn));
       load_r<BK>(vr, R, ldr, kn, kend, c0, ncols, vec_r);
     }
     // the wavefronts multiplying take issue priority over those still

@@ -74,6 +74,28 @@ def test_sample_matches_oracle(dtype, n, ncols, masked):
     assert np.all(np.abs(Sc.cpu().numpy() - ref_c) <= bound_c)
 
 
+@pytest.mark.parametrize("n", [127, 260, 1157, 2309])
+@pytest.mark.parametrize("dtype,prec", [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "f32"),
+                                        (torch.float32, "bf16x3")])
+def test_sample_any_row_alignment(dtype, prec, n):
+    """Rows of A on any entry (odd leading dimensions, a base off the 16-byte
+    grid) give the samples of an aligned copy, bit for bit: the same products
+    summed in the same order."""
+    kw = {} if prec == "f64" else {"sample_prec": prec}
+    big = torch.randn(n, n + 9, dtype=dtype, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    lo = torch.arange(n, dtype=torch.int32, device="cuda") // 60
+    Rr = P.hss_random_normal(5, 0, n, 0, 70, **kw)
+    Rc = P.hss_random_normal(5, 1, n, 0, 70, **kw)
+    for off, lda in ((0, n + 9), (1, n + 9), (3, n + 8), (2, n + 7)):
+        A = torch.as_strided(big, (n, n), (lda, 1), off)
+        pad = torch.zeros(n, (n + 15) // 4 * 4, dtype=dtype, device="cuda")
+        pad[:, :n] = A
+        print(f"sample alignment: n={n} lda={lda} offset={off} {dtype} {prec}", flush=True)
+        got = P.hss_sample(A, Rr, Rc, leaf_of=lo, **kw)
+        ref = P.hss_sample(pad[:, :n], Rr, Rc, leaf_of=lo, **kw)
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
 def _separated(d, m, seed, rank=None):
     g = np.random.default_rng(seed)
     y = g.standard_normal((d, m))
