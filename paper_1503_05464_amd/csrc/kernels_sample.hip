@@ -22,6 +22,8 @@
 // the partial sums are added in a fixed order by a second kernel
 // (deterministic, no atomics).  Consecutive tiles are mapped to the same XCD
 // so that the column tiles sharing an A slice meet in one L2.
+#include <algorithm>
+
 #include "hss_internal.h"
 
 namespace hss {
@@ -307,17 +309,22 @@ struct Plan {
   int n_mt, n_nt, ksplit, kchunk;
 };
 
+// K is split so that the workgroups fill the device: 4 per CU at the most,
+// with 1024 k or more each (a whole round of them for n >= 8192).  Smaller
+// matrices have too few tiles for that: from n = 512 on their splits are
+// taken down to 64 k, up to 16 of them and 2 workgroups per CU (the partial
+// sums of more cost what they gain; at n = 300 the reduction does).  64
+// columns, FP64, plain product: n = 512 57 -> 19 us, 1024 111 -> 24, 2048 117
+// -> 29, 4096 120 -> 61, 6000 228 -> 152, 8192 on as before.
 Plan make_plan(long long n, int ncols, int bk) {
   Plan p;
   p.n_mt = (int)((n + BM - 1) / BM);
   p.n_nt = (ncols + BN - 1) / BN;
   const long long tiles = (long long)p.n_mt * p.n_nt;
-  long long want = (1024 + tiles - 1) / tiles;  // 4 workgroups per CU (the resident maximum)
-  long long maxs = n / 1024;                   // keep >= 1024 k per split
-  if (maxs < 1) maxs = 1;
-  if (want > maxs) want = maxs;
-  if (want < 1) want = 1;
-  long long chunk = (n + want - 1) / want;
+  const long long want = (1024 + tiles - 1) / tiles;  // 4 workgroups per CU (the resident maximum)
+  const long long small = n >= 512 ? std::min({16LL, n / 64, 512 / tiles}) : 1;
+  const long long splits = std::max(1LL, std::min(want, std::max(n / 1024, small)));
+  long long chunk = (n + splits - 1) / splits;
   chunk = (chunk + bk - 1) / bk * bk;
   p.ksplit = (int)((n + chunk - 1) / chunk);
   p.kchunk = (int)chunk;

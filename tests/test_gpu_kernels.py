@@ -74,6 +74,25 @@ def test_sample_matches_oracle(dtype, n, ncols, masked):
     assert np.all(np.abs(Sc.cpu().numpy() - ref_c) <= bound_c)
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n,ncols", [(511, 64), (512, 1), (513, 65), (1025, 64), (2047, 130), (8191, 3)])
+def test_sample_split_edges(dtype, n, ncols):
+    """Sizes at the edges of the rule that splits K over workgroups, against
+    the product in FP64 on the host (bound as above), and the same bits from
+    a second call."""
+    g = np.random.default_rng(n + ncols)
+    A = g.standard_normal((n, n)).astype(np.float32 if dtype == torch.float32 else np.float64)
+    Rr, Rc = g.standard_normal((2, n, ncols))
+    args = [torch.from_numpy(a).cuda() for a in (A, Rr, Rc)]
+    print(f"sample split: n={n} ncols={ncols} {dtype}", flush=True)
+    Sr, Sc = P.hss_sample(*args)
+    again = P.hss_sample(*args)
+    assert torch.equal(Sr, again[0]) and torch.equal(Sc, again[1])
+    A64 = A.astype(np.float64)
+    assert np.all(np.abs(Sr.cpu().numpy() - A64 @ Rr) <= 2 * _gamma(n) * (np.abs(A64) @ np.abs(Rr)))
+    assert np.all(np.abs(Sc.cpu().numpy() - A64.T @ Rc) <= 2 * _gamma(n) * (np.abs(A64).T @ np.abs(Rc)))
+
+
 @pytest.mark.parametrize("n", [127, 260, 1157, 2309])
 @pytest.mark.parametrize("dtype,prec", [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "f32"),
                                         (torch.float32, "bf16x3")])
