@@ -595,10 +595,13 @@ Plan make_plan(long long n, int ncols) {
   p.n_nt = (ncols + BN - 1) / BN;
   const long long tiles = (long long)p.n_mt * p.n_nt;
   long long want = (2LL * mixed_slots() + tiles - 1) / tiles;
-  long long maxs = n / 1024;
-  if (maxs < 1) maxs = 1;
-  if (want > maxs) want = maxs;
-  if (want < 1) want = 1;
+  // 1024 k or more per split, but from n = 768 on small matrices, whose tiles
+  // leave CUs idle, are split down to one carry (64 columns, BF16x3 / FP32,
+  // plain product, us: n = 769 49 / 58 -> 37 / 43, 1500 77 / 93 -> 35 / 42,
+  // 3001 83 / 100 -> 39 / 46, 6000 72 / 89 -> 63 / 84; at n = 512 32 -> 35 for
+  // BF16x3, hence the line)
+  const long long small = n >= 768 ? std::min({16LL, n / KF, 512 / tiles}) : 1;
+  want = std::max(1LL, std::min(want, std::max(n / 1024, small)));
   long long chunk = (n + want - 1) / want;
   chunk = (chunk + KF - 1) / KF * KF;  // split boundaries on carry boundaries
   p.ksplit = (int)((n + chunk - 1) / chunk);

@@ -93,6 +93,25 @@ def test_sample_split_edges(dtype, n, ncols):
     assert np.all(np.abs(Sc.cpu().numpy() - A64.T @ Rc) <= 2 * _gamma(n) * (np.abs(A64).T @ np.abs(Rc)))
 
 
+@pytest.mark.parametrize("prec,terms", [("f32", 1), ("bf16x3", 3)])
+@pytest.mark.parametrize("n,ncols", [(767, 64), (768, 1), (1025, 65), (4097, 64)])
+def test_sample_mixed_split_edges(prec, terms, n, ncols):
+    """The reduced modes at the edges of their rule for splitting K: FP32
+    sums over at most 256 values of k (three exact terms each in BF16x3),
+    carried in FP64, so an entry errs by at most (256 terms + 8) 2^-24 of
+    |A||R|; a second call gives the same bits."""
+    A = torch.randn(n, n, dtype=torch.float32, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    Rr = P.hss_random_normal(3, 0, n, 0, ncols, sample_prec=prec)
+    Rc = P.hss_random_normal(3, 1, n, 0, ncols, sample_prec=prec)
+    print(f"sample split: n={n} ncols={ncols} {prec}", flush=True)
+    got = P.hss_sample(A, Rr, Rc, sample_prec=prec)
+    again = P.hss_sample(A, Rr, Rc, sample_prec=prec)
+    for S, S2, B, R in zip(got, again, (A, A.T), (Rr, Rc)):
+        assert torch.equal(S, S2)
+        B, R = B.double().cpu(), R.cpu()
+        assert torch.all((S.cpu() - B @ R).abs() <= (256 * terms + 8) * 2.0 ** -24 * (B.abs() @ R.abs()))
+
+
 @pytest.mark.parametrize("n", [127, 260, 1157, 2309])
 @pytest.mark.parametrize("dtype,prec", [(torch.float64, "f64"), (torch.float32, "f64"), (torch.float32, "f32"),
                                         (torch.float32, "bf16x3")])
