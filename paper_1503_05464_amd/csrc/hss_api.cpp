@@ -14,6 +14,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <optional>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -673,19 +674,25 @@ struct EventTimer {  // HIP events on the compression stream, summed at the end
   // begin, end, category (0 sample, 1 levels, 2 id, 3 sample GEMM, 4 level GEMMs, 5 gathers)
   std::vector<int> b, e, cat;
   hipStream_t s = nullptr;
-  int begin() {  // an event that cannot be made or recorded is kept as null and not timed
+  // An event that cannot be made or recorded is kept as null and not timed.
+  // It is recorded among st's launches, after the ones noted so far.
+  int begin(Staging& st) {
     hipEvent_t x = nullptr;
-    if (hipEventCreate(&x) != hipSuccess) {
-      x = nullptr;
-    } else if (hipEventRecord(x, s) != hipSuccess) {
-      (void)hipEventDestroy(x);
-      x = nullptr;
-    }
+    if (hipEventCreate(&x) != hipSuccess) x = nullptr;
+    const size_t i = ev.size();
     ev.push_back(x);
-    return (int)ev.size() - 1;
+    if (x)
+      (void)st.launch([this, i, x] {
+        if (hipEventRecord(x, s) != hipSuccess) {
+          (void)hipEventDestroy(x);
+          ev[i] = nullptr;
+        }
+        return hipSuccess;
+      });
+    return (int)i;
   }
-  void end(int bi, int c) {
-    const int ei = begin();
+  void end(int bi, int c, Staging& st) {
+    const int ei = begin(st);
     b.push_back(bi);
     e.push_back(ei);
     cat.push_back(c);
@@ -716,7 +723,7 @@ struct SampleReq {
 
 hss_status sample_batch(Handle& L, const std::vector<SampleReq>& reqs, EventTimer& tm) {
   if (reqs.empty()) return HSS_OK;
-  const int ev0 = tm.begin();
+  const int ev0 = tm.begin(L.staging);
   const int prec = L.opts.sample_prec;
   // the new random columns of every matrix and side in one launch, rounded
   // to the products' precision (used as such from here on)
@@ -740,7 +747,7 @@ hss_status sample_batch(Handle& L, const std::vector<SampleReq>& reqs, EventTime
     }
   }
   HIPCHK(launch_random_normal_batched(rj.data(), (int)rj.size(), prec, L.staging, L.stream));
-  const int evg = tm.begin();
+  const int evg = tm.begin(L.staging);
   if (prec != HSS_SAMPLE_F64 && reqs.size() > 1) {  // all matrices in one launch per side
     std::vector<SampleJob> jobs;
     for (const SampleReq& q : reqs) {
@@ -788,8 +795,8 @@ hss_status sample_batch(Handle& L, const std::vector<SampleReq>& reqs, EventTime
       L.n_sgemm += 2;
     }
   }
-  tm.end(evg, 3);
-  tm.end(ev0, 0);
+  tm.end(evg, 3, L.staging);
+  tm.end(ev0, 0, L.staging);
   // each product 2 n^2 nc flops; bytes: A once per product, R read, S written
   for (const SampleReq& q : reqs) {
     const Handle& H = *q.H;
@@ -852,7 +859,7 @@ struct Item {
 // rank readback; all handles of a batch share L's stream.
 hss_status process_items(Handle& L, Arena& W, std::vector<Item>& items, EventTimer& tm) {
   if (items.empty()) return HSS_OK;
-  const int ev_level = tm.begin();
+  const int ev_level = tm.begin(L.staging);
   auto node = [](const Item& it) -> Node& { return it.H->nodes[it.t]; };
 
   // (1) first visit: sizes, buffers, D or B
@@ -913,10 +920,14 @@ hss_status process_items(Handle& L, Arena& W, std::vector<Item>& items, EventTim
     v.cdone = 0;
     v.set_up = true;
   }
-  const int ev_g = tm.begin();
+  // the tables of this phase and the next in one copy, issued before the IDs
+  // (per level: 10 copies before, 4 now, with 16 notes for launches and events)
+  std::optional<Deferred> defer;
+  defer.emplace(L.staging, 16);
+  const int ev_g = tm.begin(L.staging);
   HIPCHK(launch_gather(items[0].A, L.dtype, items[0].lda, gath.data(), (int)gath.size(), L.staging,
                        L.stream));
-  tm.end(ev_g, 5);
+  tm.end(ev_g, 5, L.staging);
   L.gather_bytes += gather_bytes_of(gath, L.dtype);
 
   // (2) local samples of inner nodes, columns [cdone, d) (Alg. 1 / Alg. 5)
@@ -953,10 +964,12 @@ hss_status process_items(Handle& L, Arena& W, std::vector<Item>& items, EventTim
     mk(a.kc, b.kr, v.B21, a.kc, 1, b.Rc + c0, a.Sc + c0, a.perm_c, v.Sc + c0);
     mk(b.kc, a.kr, v.B12, b.kc, 1, a.Rc + c0, b.Sc + c0, b.perm_c, v.Sc + (long long)a.kc * H.ldg + c0);
   }
-  const int ev_g1 = tm.begin();
+  const int ev_g1 = tm.begin(L.staging);
   HIPCHK(launch_gemm_batched(gd.data(), (int)gd.size(), L.staging, L.stream));
-  tm.end(ev_g1, 4);
+  tm.end(ev_g1, 4, L.staging);
   L.lgemm_bytes += gemm_bytes(gd);
+  HIPCHK(defer->done());
+  defer.reset();
 
   // (3) interpolative decompositions of the nodes not yet compressed
   std::vector<int> idn;  // indices into items
@@ -990,7 +1003,7 @@ hss_status process_items(Handle& L, Arena& W, std::vector<Item>& items, EventTim
       HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&L.k_host), (size_t)np * 2 * 4, hipHostMallocDefault));
       L.k_host_cap = np * 2;
     }
-    const int ev_id = tm.begin();
+    const int ev_id = tm.begin(L.staging);
     const double t_id0 = L.verbose >= 2 ? now_ms() : 0.0;
     HIPCHK(launch_id_factor(pr.data(), np, L.opts.rtol, wk, L.work_id.cap, L.k_host, L.staging,
                             L.stream));
@@ -1038,12 +1051,14 @@ hss_status process_items(Handle& L, Arena& W, std::vector<Item>& items, EventTim
       sel.push_back(2 * (int)q);
       sel.push_back(2 * (int)q + 1);
     }
+    defer.emplace(L.staging, 16);  // from here to the end of the level: one more
     HIPCHK(launch_id_finish(pr.data(), np, L.k_host, sel.data(), (int)sel.size(), wk, L.staging,
                             L.stream));
-    tm.end(ev_id, 2);
+    tm.end(ev_id, 2, L.staging);
   }
 
   // (4) skeleton index sets of the nodes compressed now: I_tau = I_in(J)
+  if (!defer) defer.emplace(L.staging, 16);
   std::vector<IndexDesc> ix;
   for (size_t q = 0; q < items.size(); ++q) {
     if (!passed[q]) continue;
@@ -1107,12 +1122,13 @@ hss_status process_items(Handle& L, Arena& W, std::vector<Item>& items, EventTim
       gd.push_back(g);
     }
   }
-  const int ev_g2 = tm.begin();
+  const int ev_g2 = tm.begin(L.staging);
   HIPCHK(launch_gemm_batched(gd.data(), (int)gd.size(), L.staging, L.stream));
-  tm.end(ev_g2, 4);
+  tm.end(ev_g2, 4, L.staging);
   L.lgemm_bytes += gemm_bytes(gd);
   for (Item& it : items) node(it).cdone = it.d;
-  tm.end(ev_level, 1);
+  tm.end(ev_level, 1, L.staging);
+  HIPCHK(defer->done());
   // no wait here: the next level's ID readback orders the host after this
   // level, and the staging block is only reused once its readers have run
   return HSS_OK;

@@ -38,8 +38,8 @@ struct Staging {
   // While deferred, push() only fills the pinned block and launch() only
   // notes the launch: a run of small launches then pays one copy instead of
   // one each (a copy of any size takes 2 to 5 us on the stream, as long as a
-  // small kernel).  The copies are issued with the launches after 4 notes,
-  // then 8, 16, ..., so that the device starts while the host still builds
+  // small kernel).  The copies are issued with the launches after `batch`
+  // notes, then twice as many, ..., so that the device starts while the host still builds
   // the later tables.
   bool deferred = false;
   size_t copied = 0;  // bytes of the block whose copies were queued
@@ -77,14 +77,15 @@ struct Staging {
   hipError_t retire();
 };
 
-// Defers st's copies and launches while it lives.  done() issues what is left;
+// Defers st's copies and launches while it lives, the first of them until
+// `first` launches are noted.  done() issues what is left;
 // without it (an error return) what is left is dropped.
 struct Deferred {
   Staging& st;
-  explicit Deferred(Staging& s) : st(s) {
+  explicit Deferred(Staging& s, size_t first = 4) : st(s) {
     st.deferred = true;
     st.copied = st.used;
-    st.batch = 4;
+    st.batch = first;
     st.noted.clear();
   }
   hipError_t done() {

@@ -77,13 +77,17 @@ hipError_t launch_gather(const void* A, int dtype, long long lda, const GatherDe
     if (!dd) {
       err = hipErrorOutOfMemory;
     } else if (dtype == 1) {
-      hipLaunchKernelGGL(gather_kernel<float>, dim3((unsigned)rows), dim3(NT), 0, s,
-                         static_cast<const float*>(A), lda, static_cast<const DevGather*>(dd), kept);
-      err = hipGetLastError();
+      err = st.launch([=] {
+        hipLaunchKernelGGL(gather_kernel<float>, dim3((unsigned)rows), dim3(NT), 0, s,
+                           static_cast<const float*>(A), lda, static_cast<const DevGather*>(dd), kept);
+        return hipGetLastError();
+      });
     } else {
-      hipLaunchKernelGGL(gather_kernel<double>, dim3((unsigned)rows), dim3(NT), 0, s,
-                         static_cast<const double*>(A), lda, static_cast<const DevGather*>(dd), kept);
-      err = hipGetLastError();
+      err = st.launch([=] {
+        hipLaunchKernelGGL(gather_kernel<double>, dim3((unsigned)rows), dim3(NT), 0, s,
+                           static_cast<const double*>(A), lda, static_cast<const DevGather*>(dd), kept);
+        return hipGetLastError();
+      });
     }
   }
   delete[] h;
@@ -94,8 +98,10 @@ hipError_t launch_index_compose(const IndexDesc* descs, int nprob, Staging& st, 
   if (nprob <= 0) return hipSuccess;
   void* dd = st.push(descs, sizeof(IndexDesc) * nprob);
   if (!dd) return hipErrorOutOfMemory;
-  hipLaunchKernelGGL(index_kernel, dim3(nprob), dim3(NT), 0, s, static_cast<const IndexDesc*>(dd));
-  return hipGetLastError();
+  return st.launch([=] {
+    hipLaunchKernelGGL(index_kernel, dim3(nprob), dim3(NT), 0, s, static_cast<const IndexDesc*>(dd));
+    return hipGetLastError();
+  });
 }
 
 void launch_leaf_of(int n_leaves, const int* lo_dev, const int* hi_dev, int* leaf_of, hipStream_t s) {

@@ -2253,8 +2253,10 @@ hipError_t launch_id_finish(const IdProblem* probs, int nprob, const int* k_host
   const DevProb* dprobs = static_cast<const DevProb*>(st.push(h.data(), sizeof(DevProb) * nprob));
   const int* dsel = static_cast<const int*>(st.push(sel, (size_t)nsel * 4));
   if (!dprobs || !dsel) return hipErrorOutOfMemory;
-  hipLaunchKernelGGL(id_perm_kernel, dim3(nsel), dim3(NT), 0, s, dprobs, dsel, w);
-  hipError_t e = hipGetLastError();
+  hipError_t e = st.launch([=] {
+    hipLaunchKernelGGL(id_perm_kernel, dim3(nsel), dim3(NT), 0, s, dprobs, dsel, w);
+    return hipGetLastError();
+  });
   if (e != hipSuccess) return e;
   // blocked back substitution, last block first
   int maxblk = 0;
@@ -2304,8 +2306,10 @@ hipError_t launch_id_finish(const IdProblem* probs, int nprob, const int* k_host
     const DiagDesc* ddev = static_cast<const DiagDesc*>(st.push(dd.data(), dd.size() * sizeof(DiagDesc)));
     if (!ddev) return hipErrorOutOfMemory;
     const dim3 grid((unsigned)dd.size(), (unsigned)std::min(cblk, 65535));
-    hipLaunchKernelGGL(trsm_diag_kernel, grid, dim3(TW * 64), 0, s, ddev);
-    e = hipGetLastError();
+    e = st.launch([=] {
+      hipLaunchKernelGGL(trsm_diag_kernel, grid, dim3(TW * 64), 0, s, ddev);
+      return hipGetLastError();
+    });
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
