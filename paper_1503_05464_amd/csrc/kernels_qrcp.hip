@@ -186,11 +186,8 @@ __device__ __forceinline__ void cross_pair_i(int v, int& a, int& b) {
   a = (int)r[0];
   b = (int)r[1];
 }
-// The last two levels either by cross-row shuffles (ds_bpermute, through the
-// LDS crossbar) or by the permlane swaps (VALU).  The swaps serve the
-// persistent kernel (IDs 484 -> 471 ms per gauss65536 compression); the
-// reduction-heavy small-problem kernel runs 40 % slower with them and keeps
-// the shuffles.
+// Here the last two levels are cross-row shuffles (ds_bpermute, through the
+// LDS crossbar); the spread sums below take the permlane swaps.
 template <int N>
 __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
 #pragma unroll
