@@ -36,6 +36,7 @@ typedef u32x4 u32x4_a4 __attribute__((aligned(4)));  // 16 bytes from any entry 
 constexpr int BM = 128;
 constexpr int BN = 64;
 constexpr int NT = 256;
+constexpr int kSmallN = 512;  // below: K whole in one workgroup, loads for latency (SMALL)
 
 template <typename TA>
 struct Cfg;
@@ -66,7 +67,13 @@ __device__ __forceinline__ double widen(TA v) {
 // now: FP64 n = 20011 NN 1.78 -> 1.24, TN 1.18 -> 1.09; n = 32768 NN 2.71 ->
 // 2.45, TN 2.55 -> 2.34; FP32 n = 20011 NN 1.56 -> 1.05, TN 1.16 -> 1.05;
 // n = 32768 NN 2.13 -> 2.04, TN 2.10 -> 2.05.
-template <typename TA, bool TRANS>
+// SMALL (n < kSmallN): a few workgroups wait for every slice, so what counts
+// is its latency.  64 bytes of one row in FP64 too (eight lanes to a row
+// collide in the stores to LDS), and a thread of an edge tile whose own bytes
+// are there does not share the other threads' scalar loads.  Both products,
+// us, SMALL against the other form: FP64 n = 100 28.8 / 31.9, 256 52.5 / 57.5,
+// 511 109 / 122; FP32 100 30 / 32.5, 511 99 / 124.
+template <typename TA, bool TRANS, bool SMALL>
 __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
   constexpr int E = 64 / sizeof(TA), EV = 16 / sizeof(TA);
   constexpr int BK = Cfg<TA>::BK;
@@ -74,7 +81,7 @@ __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
   if (TRANS) {
     row = tid / (BM / E);
     col = (tid % (BM / E)) * E + q * EV;
-  } else if (sizeof(TA) == 8) {
+  } else if (sizeof(TA) == 8 && !SMALL) {
     row = (tid >> 3) + 32 * q;
     col = (tid & 7) * EV;
   } else {
@@ -83,17 +90,22 @@ __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
   }
 }
 
-template <typename TA, bool TRANS>
+template <typename TA, bool TRANS, bool SMALL>
 __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __restrict__ A,
                                        long long lda, int n, int i0, int k0, int kend,
                                        const int* __restrict__ leaf_of, bool need_mask) {
   constexpr int EV = 16 / sizeof(TA);
   const int rbeg = !TRANS ? i0 : k0, cbeg = !TRANS ? k0 : i0;
-  if (i0 + BM <= n && k0 + Cfg<TA>::BK <= kend) {  // the whole slice is there
+  const auto mine = [&] {  // this thread's 64 bytes of the slice are there
+    int row, col;
+    a_piece<TA, TRANS, true>(0, row, col);
+    return rbeg + row < (!TRANS ? n : kend) && cbeg + col + 4 * EV <= (!TRANS ? kend : n);
+  };
+  if (SMALL ? mine() : i0 + BM <= n && k0 + Cfg<TA>::BK <= kend) {  // or the whole slice is
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int row, col;
-      a_piece<TA, TRANS>(q, row, col);
+      a_piece<TA, TRANS, SMALL>(q, row, col);
       const u32x4_a4* p = reinterpret_cast<const u32x4_a4*>(A + (long long)(rbeg + row) * lda + cbeg + col);
       u32x4 w = *p;
       TA* t = reinterpret_cast<TA*>(&w);
@@ -105,7 +117,7 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int row, col;
-      a_piece<TA, TRANS>(q, row, col);
+      a_piece<TA, TRANS, SMALL>(q, row, col);
 #pragma unroll
       for (int e = 0; e < EV; ++e)
         v[q * EV + e] = (rbeg + row < rend && cbeg + col + e < cend)
@@ -118,7 +130,7 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int row, col;
-      a_piece<TA, TRANS>(q, row, col);
+      a_piece<TA, TRANS, SMALL>(q, row, col);
 #pragma unroll
       for (int e = 0; e < EV; ++e)
         if (rbeg + row < n && cbeg + col + e < n && leaf_of[rbeg + row] == leaf_of[cbeg + col + e])
@@ -127,13 +139,13 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
   }
 }
 
-template <typename TA, bool TRANS>
+template <typename TA, bool TRANS, bool SMALL>
 __device__ __forceinline__ void store_a(TA (*As)[BM + Cfg<TA>::PAD], const TA (&v)[64 / sizeof(TA)]) {
   constexpr int EV = 16 / sizeof(TA);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     int row, col;
-    a_piece<TA, TRANS>(q, row, col);
+    a_piece<TA, TRANS, SMALL>(q, row, col);
 #pragma unroll
     for (int e = 0; e < EV; ++e) {
       if (TRANS) As[row][col + e] = v[q * EV + e];
@@ -177,7 +189,7 @@ __device__ __forceinline__ void store_r(double (*Bs)[BN + 4], const double (&v)[
   for (int e = 0; e < ER; ++e) Bs[rr][cc + e] = v[e];
 }
 
-template <typename TA, bool TRANS>
+template <typename TA, bool TRANS, bool SMALL>
 __global__ __launch_bounds__(NT) void sample_kernel(
     const TA* __restrict__ A, long long lda, int n, const int* __restrict__ leaf_of,
     const double* __restrict__ R, long long ldr, double* __restrict__ S, long long lds, int ncols,
@@ -233,16 +245,16 @@ __global__ __launch_bounds__(NT) void sample_kernel(
 
   int k0 = kbeg;
   if (k0 < kend) {
-    load_a<TA, TRANS>(va, A, lda, n, i0, k0, kend, leaf_of, mask_for(k0));
+    load_a<TA, TRANS, SMALL>(va, A, lda, n, i0, k0, kend, leaf_of, mask_for(k0));
     load_r<BK>(vr, R, ldr, k0, kend, c0, ncols, vec_r);
-    store_a<TA, TRANS>(As, va);
+    store_a<TA, TRANS, SMALL>(As, va);
     store_r<BK>(Bs, vr);
   }
   __syncthreads();
   for (; k0 < kend; k0 += BK) {
     const int kn = k0 + BK;
     if (kn < kend) {
-      load_a<TA, TRANS>(va, A, lda, n, i0, kn, kend, leaf_of, mask_for(kn));
+      load_a<TA, TRANS, SMALL>(va, A, lda, n, i0, kn, kend, leaf_of, mask_for(kn));
       load_r<BK>(vr, R, ldr, kn, kend, c0, ncols, vec_r);
     }
     // the wavefronts multiplying take issue priority over those still
@@ -266,7 +278,7 @@ __global__ __launch_bounds__(NT) void sample_kernel(
     __builtin_amdgcn_s_setprio(0);
     __syncthreads();
     if (kn < kend) {
-      store_a<TA, TRANS>(As, va);
+      store_a<TA, TRANS, SMALL>(As, va);
       store_r<BK>(Bs, vr);
     }
     __syncthreads();
@@ -322,7 +334,7 @@ Plan make_plan(long long n, int ncols, int bk) {
   p.n_nt = (ncols + BN - 1) / BN;
   const long long tiles = (long long)p.n_mt * p.n_nt;
   const long long want = (1024 + tiles - 1) / tiles;  // 4 workgroups per CU (the resident maximum)
-  const long long small = n >= 512 ? std::min({16LL, n / 64, 512 / tiles}) : 1;
+  const long long small = n >= kSmallN ? std::min({16LL, n / 64, 512 / tiles}) : 1;
   const long long splits = std::max(1LL, std::min(want, std::max(n / 1024, small)));
   long long chunk = (n + splits - 1) / splits;
   chunk = (chunk + bk - 1) / bk * bk;
@@ -336,8 +348,9 @@ void run(const TA* A, long long lda, long long n, const int* leaf_of, int ncols,
          long long ldr, double* S, long long lds, double* work, hipStream_t s) {
   Plan p = make_plan(n, ncols, Cfg<TA>::BK);
   const long long nblocks = (long long)p.n_mt * p.n_nt * p.ksplit;
-  hipLaunchKernelGGL((sample_kernel<TA, TRANS>), dim3((unsigned)nblocks), dim3(NT), 0, s, A, lda,
-                     (int)n, leaf_of, R, ldr, S, lds, ncols, p.n_nt, p.ksplit, p.kchunk, work);
+  const auto fn = n < kSmallN ? sample_kernel<TA, TRANS, true> : sample_kernel<TA, TRANS, false>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)nblocks), dim3(NT), 0, s, A, lda, (int)n, leaf_of, R, ldr, S, lds, ncols,
+                     p.n_nt, p.ksplit, p.kchunk, work);
   if (p.ksplit > 1) {
     const long long total = n * ncols;
     hipLaunchKernelGGL(reduce_splits_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,

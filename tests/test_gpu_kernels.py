@@ -93,6 +93,26 @@ def test_sample_split_edges(dtype, n, ncols):
     assert np.all(np.abs(Sc.cpu().numpy() - A64.T @ Rc) <= 2 * _gamma(n) * (np.abs(A64).T @ np.abs(Rc)))
 
 
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n", [1, 3, 7, 15, 17, 33, 127, 129, 255, 383, 510])
+def test_sample_small_matrices(dtype, n):
+    """Matrices below the line of the K split, around the pieces of 16 and 64
+    bytes, the slices and the tiles, rows on any entry, NaN beside and below
+    the matrix: against the product in FP64 on the host (bound as above)."""
+    g = np.random.default_rng(n)
+    pad = np.full((n + 1, n + 3), np.nan, dtype=np.float32 if dtype == torch.float32 else np.float64)
+    pad[:n, :n] = g.standard_normal((n, n))
+    A64 = pad[:n, :n].astype(np.float64)
+    lo = np.arange(n, dtype=np.int32) // 20
+    A64[lo[:, None] == lo[None, :]] = 0.0
+    Rr, Rc = g.standard_normal((2, n, 5))
+    print(f"small sample: n={n} {dtype}", flush=True)
+    Sr, Sc = P.hss_sample(torch.from_numpy(pad).cuda()[:n, :n], torch.from_numpy(Rr).cuda(),
+                          torch.from_numpy(Rc).cuda(), leaf_of=torch.from_numpy(lo).cuda())
+    assert np.all(np.abs(Sr.cpu().numpy() - A64 @ Rr) <= 2 * _gamma(n) * (np.abs(A64) @ np.abs(Rr)))
+    assert np.all(np.abs(Sc.cpu().numpy() - A64.T @ Rc) <= 2 * _gamma(n) * (np.abs(A64).T @ np.abs(Rc)))
+
+
 @pytest.mark.parametrize("prec,terms", [("f32", 1), ("bf16x3", 3)])
 @pytest.mark.parametrize("n,ncols", [(767, 64), (768, 1), (1025, 65), (4097, 64)])
 def test_sample_mixed_split_edges(prec, terms, n, ncols):
