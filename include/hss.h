@@ -496,8 +496,12 @@ hss_status hss_sample_noalloc(const void* A, int dtype, int sample_prec, long lo
  *           M x K (A_p is M x K with lda >= K, or K x M with lda >= M if
  *           transA), B_p is K x N (ldb >= N), C_p is M x N (ldc >= N).  C_p
  *           must not overlap A_p or B_p.
- *  variant  tile shape 0 .. hss_gemm_variants()-1, or < 0 for the shape the
- *           tuning table gives the batch's size class (what the library uses).
+ *  variant  tile shape 0 .. hss_gemm_variants()-1, or < 0 for the shape that
+ *           the library takes for its own products: the one the tuning table
+ *           gives the batch's size class, or, where the tiles do not fill the
+ *           device, one whose longest product is through soonest.  Every shape
+ *           gives the same bits.  A batch with an A whose rows lie so far
+ *           apart that a tile spans 4 GiB runs in one shape of its own.
  * Stream-ordered.  HSS_ERR_ARG for invalid sizes or a variant out of range.
  */
 hss_status hss_gemm_batched(int nprob, const int* M, const int* N, const int* K, const double* const* A,

@@ -543,8 +543,8 @@ def hss_gemm_variants() -> int:
 def hss_gemm_batched(As, Bs, Cs, transA=None, alpha=1.0, beta=0.0, variant=-1, stream=None):
     """C_p = alpha op(A_p) B_p + beta C_p for lists of CUDA float64 matrices
     (row-major, unit column stride), in one launch of the library's batched
-    GEMM with tile shape `variant` (-1: the tuning table's choice).  Returns
-    Cs."""
+    GEMM with tile shape `variant` (-1: the shape the library takes for its
+    own products).  Returns Cs."""
     nprob = len(As)
     if not (len(Bs) == len(Cs) == nprob):
         raise ValueError("one B and one C per A")

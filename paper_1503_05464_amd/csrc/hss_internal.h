@@ -208,8 +208,8 @@ struct GemmDesc {
   double alpha, beta;
 };
 // Runs all problems of `descs` (host array) in one launch, with the tile
-// shape `variant` (0 .. gemm_variants()-1) or, for variant < 0, the one the
-// tuning table gives the batch's size class.
+// shape `variant` (0 .. gemm_variants()-1) or, for variant < 0, the one that
+// the tuning table or the launch's longest product calls for (pick_shape).
 hipError_t launch_gemm_batched(const GemmDesc* descs, int nprob, Staging& st, hipStream_t s,
                                int variant = -1);
 int gemm_variants();

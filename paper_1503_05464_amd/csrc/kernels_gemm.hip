@@ -34,12 +34,13 @@
 #include <cstring>
 #include <vector>
 
+#include "gemm_offsets.h"
 #include "hss_internal.h"
 
 namespace hss {
 namespace {
 
-constexpr int TK = 16, NTH = 256;
+constexpr int TK = kGemmSlice, NTH = 256;
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
@@ -92,7 +93,7 @@ __device__ __forceinline__ void lds_barrier() {
 
 // k is walked in chunks of KC: the rows of B of a chunk are looked up ahead,
 // as addresses in LDS, and A is addressed from the chunk's first k
-constexpr int KC = 512;
+constexpr int KC = kGemmChunk;
 static_assert(KC % TK == 0, "whole slices");
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -108,10 +109,14 @@ __device__ __forceinline__ double buf_load(__amdgpu_buffer_rsrc_t r, unsigned la
 // Held to four wavefronts per SIMD (at most 128 registers), or to three where
 // the LDS of a tile of 128 rows leaves no room for more, or where four blocks
 // per wavefront would spill.
-template <int WGM, int WGN, int MB, int NB>
+// FAR: A is read at 64-bit addresses, for a leading dimension at which 32-bit
+// offsets would wrap (gemm_offsets_fit: from 1048575 on with 512 rows of a
+// transposed A, from 4.2 million on without).
+template <int WGM, int WGN, int MB, int NB, bool FAR = false>
 __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 4 || MB * NB > 2 ? 3 : 4))) void gemm_batched_kernel(
     const DevDesc* __restrict__ descs, const long long* __restrict__ tile0, int nprob) {
   using TL = Tile<WGM, WGN, MB, NB>;
+  static_assert(TL::TM <= kGemmMaxRows, "offsets are checked for tiles of at most kGemmMaxRows rows");
   constexpr int TM = TL::TM, TN = TL::TN, LA = TL::LA, LB = TL::LB, PD = TL::PD;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -169,7 +174,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
   // that are not stored), and k past the end is zeroed on its way into LDS.
   // A is read through a buffer resource: a lane's offset never changes, the
   // slice's is a scalar, and reads past the matrix return zero.
-  unsigned ao[LA];     // byte offset of the entry from the chunk's first slice
+  unsigned ao[LA];     // byte offset of the entry from the chunk's first slice (FAR: its row)
   int ak[LA], al[LA];  // k within the slice, place in the LDS slice
 #pragma unroll
   for (int q = 0; q < LA; ++q) {
@@ -178,17 +183,26 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
     ak[q] = tr ? e / TM : e % TK;
     al[q] = ak[q] * (TM + 4) + rr;
     const int rv = min(rr, M - 1 - r0);
-    ao[q] = 8u * (unsigned)(tr ? (long long)ak[q] * g.lda + rv : (long long)rv * g.lda + ak[q]);
+    ao[q] = FAR ? (unsigned)rv : gemm_entry_offset(tr, g.lda, rv, ak[q]);
   }
-  const unsigned astep = 8u * (unsigned)(tr ? TK * g.lda : TK);  // from one slice to the next
+  const unsigned astep = gemm_slice_step(tr, g.lda);  // from one slice to the next
   const int mt = min(TM, M - r0);  // rows of this tile
   const int cb = min(c0 + tid % TN, N - 1);
   const int bk = tid / TN;  // entries q of B lie NTH / TN rows apart
   double va[PD][LA], vb[PD][LB];
   __amdgpu_buffer_rsrc_t ra;
+  gdouble_c* fa = nullptr;  // FAR: the chunk's first entry
+  int fk = 0;               // and its last k
   auto load = [&](double (&xa)[LA], double (&xb)[LB], int s) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < LA; ++q) xa[q] = buf_load(ra, ao[q], (unsigned)s * astep);
+    for (int q = 0; q < LA; ++q) {
+      if constexpr (FAR) {
+        const long long k = min(s * TK + ak[q], fk), r = ao[q];
+        xa[q] = fa[tr ? k * g.lda + r : r * g.lda + k];
+      } else {
+        xa[q] = buf_load(ra, ao[q], (unsigned)s * astep);
+      }
+    }
 #pragma unroll
     for (int q = 0; q < LB; ++q) xb[q] = ((gdouble_c*)krow[s * TK + bk + q * (NTH / TN)])[cb];
   };
@@ -216,9 +230,14 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
       const int kk = kc + min(k, kn - 1);
       krow[k] = (uintptr_t)seg_row(g.B, g.B.map ? as_global(g.B.map)[kk] : kk);
     }
-    ra = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<double*>(g.A + (tr ? (long long)kc * g.lda + r0 : (long long)r0 * g.lda + kc)), 0,
-        buf_range(tr ? (kn - 1) * g.lda + mt : (mt - 1) * g.lda + kn), 0x00027000);
+    const double* a0 = g.A + (tr ? (long long)kc * g.lda + r0 : (long long)r0 * g.lda + kc);
+    if constexpr (FAR) {
+      fa = (gdouble_c*)(uintptr_t)a0;
+      fk = kn - 1;
+    } else {
+      ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(a0), 0,
+                                             buf_range(tr ? (kn - 1) * g.lda + mt : (mt - 1) * g.lda + kn), 0x00027000);
+    }
     lds_barrier();
 #pragma unroll
     for (int p = 0; p < PD; ++p) load(va[p], vb[p], min(p, ns - 1));
@@ -292,6 +311,8 @@ const GVariant kGVariants[] = {
     {128, 32, gemm_batched_kernel<4, 1, 2, 2>},
     {16, 64, gemm_batched_kernel<1, 4, 1, 1>},
 };
+// the shape of every launch with an A beyond 32-bit offsets
+const GVariant kGFar = {32, 32, gemm_batched_kernel<2, 2, 1, 1, true>};
 constexpr int kNumGVariants = sizeof(kGVariants) / sizeof(kGVariants[0]);
 
 #include "gemm_tiles.inc"  // kGemmTileTable[class] = variant (written by autotune.py)
@@ -359,7 +380,12 @@ hipError_t launch_gemm_batched(const GemmDesc* descs, int nprob, Staging& st, hi
     }();
     if (forced >= 0 && forced < kNumGVariants) variant = forced;
   }
-  const GVariant& gv = kGVariants[variant];
+  bool far = false;
+  for (int p = 0; p < nprob; ++p) {
+    const GemmDesc& g = descs[p];
+    far = far || (g.M > 0 && g.N > 0 && !gemm_offsets_fit(g.transA != 0, g.M, g.K, g.lda));
+  }
+  const GVariant& gv = far ? kGFar : kGVariants[variant];
   std::vector<DevDesc> h;
   std::vector<long long> tile0;  // first flattened tile of each problem
   h.reserve(nprob);

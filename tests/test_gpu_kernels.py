@@ -483,3 +483,29 @@ def test_gemm_batched_long_inner_dimensions(K):
         for o, f, r, bd in zip(out, first, ref, bnd):
             assert np.all(np.abs(o.cpu().numpy() - r) <= bd)
             assert torch.equal(o, f)
+
+
+@pytest.mark.parametrize("M,N,K,t,lda", [
+    (70, 40, 520, 1, 1_048_000),   # offsets reach almost 2^32 bytes
+    (70, 40, 520, 1, 1_100_000),   # the last slices of a chunk lie beyond
+    (70, 40, 1041, 1, 540_000),    # three chunks, each within
+    (3, 5, 40, 1, 16_000_000),     # a few rows far apart
+    (130, 17, 37, 0, 4_150_000),   # without transposition: a tile of 128 rows almost there
+    (130, 17, 37, 0, 4_250_000),   # and beyond
+])
+def test_gemm_batched_far_apart_rows(M, N, K, t, lda):
+    """Rows of A so far apart that 32-bit offsets reach, or no longer reach,
+    the last of a tile: the same bits as from a compact copy of A, in the
+    shape the library picks and in one that is asked for."""
+    g = torch.Generator("cuda").manual_seed(lda)
+    rows, cols = (K, M) if t else (M, K)
+    print(f"gemm_batched lda={lda} trans={t}", flush=True)
+    A = torch.empty((rows - 1) * lda + cols, dtype=torch.float64, device="cuda").as_strided((rows, cols), (lda, 1))
+    A.copy_(torch.randn(rows, cols, dtype=torch.float64, device="cuda", generator=g))
+    B = torch.randn(K, N, dtype=torch.float64, device="cuda", generator=g)
+    C = torch.empty(M, N, dtype=torch.float64, device="cuda")
+    ref = P.hss_gemm_batched([A.contiguous()], [B], [C.clone()], [t])[0]
+    for v in (-1, 2):
+        assert torch.equal(P.hss_gemm_batched([A], [B], [C.clone()], [t], variant=v)[0], ref)
+    exact = (A.T if t else A).cpu() @ B.cpu()
+    assert torch.allclose(ref.cpu(), exact, rtol=0, atol=2 * _gamma(K) * float((A.abs().max() * B.abs().max())) * K)

@@ -1,0 +1,72 @@
+"""CPU checks of native rules that need no device: small C++ programs compiled
+against the library's own headers."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1503_05464_amd", "csrc")
+
+
+def _run(tmp_path, source, *flags):
+    src, exe = tmp_path / "check.cpp", tmp_path / "check"
+    src.write_text(source)
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(exe), str(src), *flags],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+GEMM_OFFSETS = r"""
+#include <cstdio>
+#include <initializer_list>
+#include "gemm_offsets.h"
+using namespace hss;
+int main() {
+  long long fit = 0, far = 0;
+  for (bool tr : {false, true})
+    for (int M : {1, 2, 33, 128, 700})
+      for (int K : {1, 15, 16, 17, 40, 511, 512, 513, 3000})
+        for (long long base : {700LL, 1048576LL, 1050628LL, 1082402LL, 4194304LL, 8388608LL, 33554432LL, 536870911LL,
+                               1LL << 31, 1LL << 40})
+          for (long long d = -3; d <= 3; ++d) {
+            const long long lda = base + d;
+            if (lda < (tr ? M : K)) continue;
+            if (!gemm_offsets_fit(tr, M, K, lda)) {
+              ++far;
+              continue;
+            }
+            ++fit;
+            // every corner of the largest tile's first and last slice
+            const int rows = M < kGemmMaxRows ? M : kGemmMaxRows;
+            const int ns = ((K < kGemmChunk ? K : kGemmChunk) + kGemmSlice - 1) / kGemmSlice;
+            for (int s : {0, ns - 1})
+              for (int k : {0, kGemmSlice - 1})
+                for (int r : {0, rows - 1}) {
+                  const long long kk = (long long)s * kGemmSlice + k;
+                  const long long want = 8 * (tr ? kk * lda + r : r * lda + kk);
+                  const unsigned got = gemm_entry_offset(tr, lda, r, k) + (unsigned)s * gemm_slice_step(tr, lda);
+                  if (got != want || want + 8 > 0xffffffffLL) {
+                    std::printf("tr %d M %d K %d lda %lld s %d k %d r %d: %u for %lld\n", tr, M, K, lda, s, k, r, got, want);
+                    return 1;
+                  }
+                }
+          }
+  // the first leading dimensions whose last slice wraps, and ordinary ones
+  const bool ok = !gemm_offsets_fit(true, 64, 512, 1082402) && !gemm_offsets_fit(true, 64, 3000, 1050628) &&
+                  !gemm_offsets_fit(false, 128, 64, 4300000) && !gemm_offsets_fit(false, 64, 16, 8500000) &&
+                  gemm_offsets_fit(true, 64, 3000, 1048000) && gemm_offsets_fit(true, 64, 16, 30000000) &&
+                  gemm_offsets_fit(false, 700, 3000, 4190000) && gemm_offsets_fit(false, 1, 64, 1 << 28);
+  std::printf("%lld fit, %lld far\n", fit, far);
+  return ok && fit > 100 && far > 100 ? 0 : 2;
+}
+"""
+
+
+def test_gemm_offsets_of_a(tmp_path):
+    """The batched GEMM's 32-bit offsets of A equal the 64-bit ones wherever
+    its rule takes them, for leading dimensions around every place where one
+    of their terms wraps; where they would wrap the rule says so."""
+    _run(tmp_path, GEMM_OFFSETS)
