@@ -195,7 +195,7 @@ hss_status hss_matvec_batched(int nmat, const hss_handle* h, int nrhs, const dou
  * Host-synchronous.  A second call on a factored handle does nothing.
  * Returns HSS_OK, HSS_ERR_ARG (NULL handle), HSS_ERR_STATE (not
  * compressed), HSS_ERR_ALLOC, HSS_ERR_HIP or HSS_ERR_SINGULAR (a zero pivot
- * in the root LU). */
+ * in the root LU, or a column of it with nothing but NaN). */
 hss_status hss_factor(hss_handle h, void* stream);
 
 /* Solve A_HSS x = b after hss_factor (Alg. 4).  b, x: DEVICE n x nrhs

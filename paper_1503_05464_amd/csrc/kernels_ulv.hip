@@ -264,7 +264,8 @@ __global__ __launch_bounds__(64) void larft_kernel(const LarftDesc* __restrict__
 // ld), one workgroup.  Pivot rows are chosen by largest magnitude (lowest
 // index on ties) and swapped inside the panel; piv[j0 + c] = absolute row
 // chosen for column j0 + c.  info is set to the first zero pivot (1-based) or
-// left untouched.
+// left untouched.  A column with nothing but NaN left has no largest entry: it
+// counts as a zero pivot and its row stays, so no index leaves the matrix.
 __global__ __launch_bounds__(1024) void lu_panel_kernel(double* __restrict__ A, long long ld, int n,
                                                        int j0, int nb, int* __restrict__ piv,
                                                        int* __restrict__ info) {
@@ -297,6 +298,7 @@ __global__ __launch_bounds__(1024) void lu_panel_kernel(double* __restrict__ A, 
           v = rv[q];
           ix = ri[q];
         }
+      if (ix == INT_MAX) ix = col;  // nothing but NaN
       s_p = ix;
       piv[col] = ix;
       if (!(v > 0.0) && *info == 0) *info = col + 1;
@@ -387,6 +389,7 @@ __global__ __launch_bounds__(NTH) void lu_panel_reg_kernel(double* __restrict__ 
             v = rv[q];
             ix = ri[q];
           }
+        if (ix == INT_MAX) ix = col;  // nothing but NaN
         s_p = ix;
         piv[col] = ix;
         if (!(v > 0.0) && *info == 0) *info = col + 1;

@@ -219,3 +219,25 @@ def test_root_solve_sizes_and_range(n, nrhs):
     err = np.linalg.norm(xs[0] - ref, axis=0) / np.linalg.norm(ref, axis=0)
     assert np.all(err <= 10 * n * 2.0 ** -53 * np.linalg.cond(A)), err.max()
     assert np.array_equal(xs[0], xs[1])
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n", [1, 9, 300, 600, 1100, 2100, 4200])
+def test_factor_of_non_finite_matrix(n, bad):
+    """Root LU (one leaf, A = D) of a matrix with one entry that is not
+    finite, in every panel kernel.  Elimination spreads a NaN until a column
+    has nothing else left and no pivot to choose: no interchange then, and a
+    singular matrix.  An infinity becomes NaN only if its row is chosen before
+    its column (0 or a finite multiplier times infinity, subtracted from
+    another): it may also be a pivot like any other."""
+    A = torch.randn(n, n, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(n))
+    A[n // 2, n // 3] = bad
+    print(f"factor of a matrix with {bad}: n={n}", flush=True)
+    h = P.hss_compress(A, leaf_size=max(256, n))
+    status = P.HSS_OK
+    try:
+        P.hss_factor(h)
+    except P.HSSError as e:
+        status = e.status
+    assert status == P.HSS_ERR_SINGULAR or (bad == float("inf") and status == P.HSS_OK)
+    P.hss_destroy(h)
