@@ -40,6 +40,7 @@
 #include <vector>
 
 #include "hss_internal.h"
+#include "quotient.h"
 
 namespace hss {
 namespace {
@@ -1488,18 +1489,15 @@ __device__ __forceinline__ gdouble* as_global(const double* p) { return (gdouble
 
 // A wavefront solves TC columns at once, lane a holding x[a]: row b of Rt is
 // applied once x[b] is final, read from its lane by all others.  Entries at
-// and past b meet a zero of Rt, so the fast form needs no select; the plain
-// one (a diagonal outside 2^+-500, or a result that is not finite) divides
-// in place and leaves the entries past b alone.
+// and past b meet a zero of Rt, so the fast form needs no select (and keeps
+// what each lane divides until its last line); the plain one (a diagonal
+// outside 2^+-500, or a quotient that quot_by may round otherwise) divides in
+// place and leaves the entries past b alone.
 constexpr int TC = 8, TW = 4;  // columns per wavefront, wavefronts
 template <bool PLAIN>
-__device__ __forceinline__ void trsm_diag_solve(double (&x)[TC], const double (*Rt)[64], int nb, double d, double r) {
+__device__ __forceinline__ bool trsm_diag_solve(double (&x)[TC], const double (*Rt)[64], int nb, double d, double r) {
   const int lane = threadIdx.x & 63;
-  auto quot = [&](double v) {
-    if (PLAIN) return v / d;
-    const double q = v * r;  // correctly rounded reciprocal: one Newton step gives the quotient
-    return fma(fma(-q, d, v), r, q);
-  };
+  auto quot = [&](double v) { return PLAIN ? v / d : quot_by(v, d, r); };
   constexpr int U = 4;  // rows read ahead
   for (int b0 = nb - 1; b0 > 0; b0 -= U) {
     double t[U];
@@ -1517,8 +1515,14 @@ __device__ __forceinline__ void trsm_diag_solve(double (&x)[TC], const double (*
       }
     }
   }
+  bool same = true;
 #pragma unroll
-  for (int c = 0; c < TC; ++c) x[c] = quot(x[c]);
+  for (int c = 0; c < TC; ++c) {
+    const double num = x[c];
+    x[c] = quot(num);
+    if (!PLAIN) same = same && (lane >= nb || quot_same(num, x[c]));
+  }
+  return same;
 }
 
 // blockIdx.x the block, grid y strides its columns.  What bounds it: the
@@ -1568,11 +1572,7 @@ __global__ __launch_bounds__(TW * 64) void trsm_diag_kernel(const DiagDesc* __re
   while (c0 < g.nrest) {
     bool again = plain;
     if (!again) {
-      trsm_diag_solve<false>(x, Rt, nb, d, r);
-      bool fin = true;
-#pragma unroll
-      for (int c = 0; c < TC; ++c) fin = fin && fabs(x[c]) <= 1.7976931348623157e308;
-      again = __any(!fin);
+      again = __any(!trsm_diag_solve<false>(x, Rt, nb, d, r));
       if (again) load_x();
     }
     if (again) trsm_diag_solve<true>(x, Rt, nb, d, r);

@@ -9,6 +9,7 @@
 
 #include "hss_internal.h"
 #include "hss_ulv_kernels.h"
+#include "quotient.h"
 
 namespace hss {
 namespace {
@@ -120,15 +121,6 @@ __device__ __forceinline__ double lane_bcast(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// x / d by d's correctly rounded reciprocal r: one Newton step on the
-// quotient gives the correctly rounded quotient (Markstein) while nothing
-// leaves the exponent range; an infinite quotient is returned as it is.
-__device__ __forceinline__ double div_by(double x, double d, double r) {
-  const double q0 = x * r;
-  const double q = fma(fma(-q0, d, x), r, q0);
-  return fabs(q0) <= 1.7976931348623157e308 ? q : q0;
-}
-
 // The same block solve for few right-hand sides: one wavefront per column,
 // lane r holding x[r].  Column c of T is applied once x[c] is final, which
 // is then read from its lane by all others, so a column takes nb dependent
@@ -140,11 +132,13 @@ __device__ __forceinline__ double div_by(double x, double d, double r) {
 // of T come from LDS ahead of the chain (eight steps unrolled), staged with
 // every load in flight: 17.5 -> 7.6 us
 // per launch of 64-row blocks, against a division and two LDS latencies in
-// every step.  A diagonal outside 2^+-500 takes the plain division.
+// every step.  A diagonal outside 2^+-500, or a quotient that quot_by may
+// round otherwise, takes the plain division: the whole block again.
 template <bool LOWER, bool PLAIN>
-__device__ __forceinline__ double tri_wave_solve(const double (*T)[65], int nb, double x) {
+__device__ __forceinline__ double tri_wave_solve(const double (*T)[65], int nb, double x, bool& same) {
   const int lane = threadIdx.x & 63;
   const double d = T[lane][lane], r = 1.0 / d;
+  double num = 0.0;  // what this lane divided
   constexpr int U = 8;
   for (int s0 = 0; s0 < nb; s0 += U) {
     double t[U];
@@ -154,10 +148,12 @@ __device__ __forceinline__ double tri_wave_solve(const double (*T)[65], int nb, 
     for (int u = 0; u < U; ++u) {
       const int c = LOWER ? s0 + u : nb - 1 - s0 - u;
       if (c < 0) break;  // rows past nb (LOWER) are the identity's: x = 0 there
-      const double xc = lane_bcast(PLAIN ? x / d : div_by(x, d, r), c);
+      const double xc = lane_bcast(PLAIN ? x / d : quot_by(x, d, r), c);
+      if (!PLAIN && lane == c) num = x;
       x = lane == c ? xc : ((LOWER ? lane > c : lane < c) ? fma(-t[u], xc, x) : x);
     }
   }
+  same = PLAIN || !__any(!quot_same(num, x));
   return x;
 }
 
@@ -186,10 +182,11 @@ __global__ __launch_bounds__(NT) void tri_wave_kernel(const TriDesc* __restrict_
   __syncthreads();
   if (col >= g.nrhs) return;
   x = lane < nb ? x : 0.0;
+  const double x0 = x;
   const double dd = fabs(T[lane][lane]);
-  const bool plain = __any(!(dd > 0x1p-500 && dd < 0x1p500));
-  if (g.lower) x = plain ? tri_wave_solve<true, true>(T, nb, x) : tri_wave_solve<true, false>(T, nb, x);
-  else x = plain ? tri_wave_solve<false, true>(T, nb, x) : tri_wave_solve<false, false>(T, nb, x);
+  bool same = !__any(!(dd > 0x1p-500 && dd < 0x1p500));
+  if (same) x = g.lower ? tri_wave_solve<true, false>(T, nb, x0, same) : tri_wave_solve<false, false>(T, nb, x0, same);
+  if (!same) x = g.lower ? tri_wave_solve<true, true>(T, nb, x0, same) : tri_wave_solve<false, true>(T, nb, x0, same);
   if (lane < nb) *xp = x;
 }
 

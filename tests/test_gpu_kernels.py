@@ -374,6 +374,23 @@ def test_id_block_solve_edges(k, nrest):
     assert big[0] == k and np.array_equal(big[1], one[1]) and np.array_equal(big[2], one[2])
 
 
+@pytest.mark.parametrize("lo,hi", [(-1074, -1010), (-1010, -940), (-60, -20)])
+def test_id_quotients_over_the_exponent_range(lo, hi):
+    """Y = [diag(v), T] with v falling and T small: step i's pivot is column
+    i, its reflector changes the sign of row i, so that R1 = -diag(v), R2 =
+    -T, and E = (R1^{-1} R2)^T holds one correctly rounded quotient per entry,
+    whatever its size."""
+    g = np.random.default_rng(2000 + lo)
+    d, rest = 64, 40
+    v = np.linspace(1.9, 1.0, d)
+    T = np.ldexp(g.uniform(1.0, 2.0, (d, rest)) * g.choice([-1.0, 1.0], (d, rest)), g.integers(lo, hi, (d, rest)))
+    y = np.concatenate([np.diag(v), T], axis=1)
+    print(f"ID quotients: 2^{lo} .. 2^{hi}", flush=True)
+    k, perm, E = P.hss_id_batched([torch.from_numpy(np.ascontiguousarray(y.T)).cuda()], 1e-14)[0]
+    assert k == d and np.array_equal(perm, np.arange(d + rest))
+    assert np.array_equal(E, (T / v[:, None]).T)
+
+
 @pytest.mark.parametrize("d,widest", [(250, 16), (384, 12), (500, 10), (760, 7), (1000, 6), (1270, 4),
                                       (1500, 4), (1790, 3), (2040, 3), (2300, 3), (2500, 2)])
 def test_persistent_widths_agree(d, widest, monkeypatch, capfd):

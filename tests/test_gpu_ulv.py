@@ -241,3 +241,18 @@ def test_factor_of_non_finite_matrix(n, bad):
         status = e.status
     assert status == P.HSS_ERR_SINGULAR or (bad == float("inf") and status == P.HSS_OK)
     P.hss_destroy(h)
+
+
+@pytest.mark.parametrize("lo,hi", [(-1074, -1010), (-1010, -940), (-60, 60), (960, 1021)])
+def test_solve_quotients_over_the_exponent_range(lo, hi):
+    """A diagonal matrix of one leaf: L is the identity and x = b / d, each
+    entry one quotient of the block solve, correctly rounded whatever its
+    size (subnormal dividends and quotients included)."""
+    g = np.random.default_rng(2000 + hi)
+    n, nrhs = 64, 64
+    d = g.uniform(1.0, 2.0, n) * 2.0 ** g.integers(-3, 3, n)
+    b = np.ldexp(g.uniform(1.0, 2.0, (n, nrhs)) * g.choice([-1.0, 1.0], (n, nrhs)), g.integers(lo, hi, (n, nrhs)))
+    print(f"solve quotients: 2^{lo} .. 2^{hi}", flush=True)
+    h = P.hss_compress(torch.from_numpy(np.diag(d)).cuda(), leaf_size=256)
+    P.hss_factor(h)
+    assert np.array_equal(P.hss_solve(h, torch.from_numpy(b).cuda()).cpu().numpy(), b / d[:, None])
