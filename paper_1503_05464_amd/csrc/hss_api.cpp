@@ -513,19 +513,17 @@ void* Staging::push(const void* src, size_t bytes) {
 }
 
 hipError_t Staging::issue() {
+  if (!deferred) return hipSuccess;  // push() has copied, launch() has run
+  if (failed != hipSuccess) return failed;
   if (host && used > copied) {
     stream_used = true;
-    const hipError_t e = hipMemcpyAsync(dev + copied, host + copied, used - copied, hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess) return e;
-    copied = used;
+    failed = hipMemcpyAsync(dev + copied, host + copied, used - copied, hipMemcpyHostToDevice, stream);
+    if (failed == hipSuccess) copied = used;
   }
-  for (auto& f : noted) {
-    const hipError_t e = f();
-    if (e != hipSuccess) return e;
-  }
+  for (size_t q = 0; q < noted.size() && failed == hipSuccess; ++q) failed = noted[q]();
   noted.clear();
   batch = std::min<size_t>(batch * 2, 256);
-  return hipSuccess;
+  return failed;
 }
 
 bool Staging::reserve(std::initializer_list<size_t> sizes) {

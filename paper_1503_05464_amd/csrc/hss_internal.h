@@ -45,15 +45,20 @@ struct Staging {
   size_t copied = 0;  // bytes of the block whose copies were queued
   size_t batch = 4;   // launches noted before they are issued
   std::vector<std::function<hipError_t()>> noted;
+  hipError_t failed = hipSuccess;  // the first error of what was issued while deferred
   // Runs f (a kernel launch, or anything queued on `stream`) now, or when
   // the launches noted before it are issued.
   template <typename F>
   hipError_t launch(F&& f) {
     if (!deferred) return f();
+    if (failed != hipSuccess) return failed;
     noted.emplace_back(std::forward<F>(f));
     return noted.size() >= batch ? issue() : hipSuccess;
   }
-  // One copy of everything pushed since the last one, then the noted launches.
+  // One copy of everything pushed since the last one, then the noted launches,
+  // up to the first that fails: none runs twice, and from then on this,
+  // launch() and Deferred::done() return that error, so that a caller may
+  // leave a launch's own status unread (a timing event).
   hipError_t issue();
   // Takes a block of at least `bytes` (a retired one whose readers have run,
   // or a new one).
@@ -87,6 +92,7 @@ struct Deferred {
     st.copied = st.used;
     st.batch = first;
     st.noted.clear();
+    st.failed = hipSuccess;
   }
   hipError_t done() {
     const hipError_t e = st.issue();

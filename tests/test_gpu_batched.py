@@ -196,3 +196,26 @@ def test_batched512_full_size():
                                             leaf_size=kw["leaf_size"], p_margin=kw["p_margin"],
                                             sample_prec=kw["sample_prec"]))
         assert abs(P.hss_stats(hs[q])["d_final"] - Ho.d_final) <= kw["dd"]
+
+
+def test_descriptor_tables_beyond_one_block():
+    """Small leaves give a matvec and a solve thousands of products: the
+    tables of one call (about 190 bytes a product, 2300 products a handle and
+    matvec) outgrow the 1 MiB staging block while launches still wait for
+    their copy.  The batched matvec equals the single ones, each within a
+    block, bit for bit; the solve undoes the matvec."""
+    n, count = 4096, 6
+    T = torch.from_numpy(W.toeplitz_inverse_distance(n)).cuda()
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    hs = [P.hss_compress(T + q * eye, rtol=1e-10, d0=64, dd=32, leaf_size=16, seed=q) for q in range(1, count + 1)]
+    xs = [torch.from_numpy(W.uniform_rhs(n, 3, q)).cuda() for q in range(count)]
+    assert sum(P.hss_stats(h)["n_nodes"] for h in hs) >= 3000
+    print(f"staging overflow: {count} handles of {P.hss_stats(hs[0])['n_nodes']} nodes", flush=True)
+    for _ in range(2):
+        single = [P.hss_matvec(h, x) for h, x in zip(hs, xs)]
+        for b, b1 in zip(P.hss_matvec_batched(hs, xs), single):
+            assert torch.equal(b, b1)
+    h, x, b = hs[0], xs[0], single[0]
+    P.hss_factor(h)
+    for _ in range(2):  # cond(T + I) is below 20: the residual of a backward stable solve
+        assert float((P.hss_solve(h, b) - x).norm() / x.norm()) <= 1e-10

@@ -3,17 +3,17 @@ against the library's own headers."""
 import os
 import subprocess
 
-import pytest
+import paper_1503_05464_amd as P
+from paper_1503_05464_amd import build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1503_05464_amd", "csrc")
 
 
-def _run(tmp_path, source, *flags):
+def _run(tmp_path, source, compiler=("g++", "-std=c++17", "-O1", "-Wall", "-Werror"), flags=()):
     src, exe = tmp_path / "check.cpp", tmp_path / "check"
     src.write_text(source)
-    r = subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC, "-o", str(exe), str(src), *flags],
-                       capture_output=True, text=True)
+    r = subprocess.run([*compiler, "-I", CSRC, "-o", str(exe), str(src), *flags], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
@@ -70,3 +70,53 @@ def test_gemm_offsets_of_a(tmp_path):
     its rule takes them, for leading dimensions around every place where one
     of their terms wraps; where they would wrap the rule says so."""
     _run(tmp_path, GEMM_OFFSETS)
+
+
+STAGING = r"""
+#include <cstdio>
+#include "hss_internal.h"
+using namespace hss;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
+int main() {
+  Staging st;
+  int ran[8] = {0};
+  auto note = [&](int q, hipError_t e) { return st.launch([&ran, q, e] { ++ran[q]; return e; }); };
+  {  // noted until the fourth, then run in order, once
+    Deferred d(st);
+    CHECK(note(0, hipSuccess) == hipSuccess && note(1, hipSuccess) == hipSuccess && note(2, hipSuccess) == hipSuccess);
+    CHECK(ran[0] == 0 && ran[2] == 0);
+    CHECK(note(3, hipSuccess) == hipSuccess && ran[0] == 1 && ran[3] == 1);
+    CHECK(note(4, hipSuccess) == hipSuccess && ran[4] == 0 && d.done() == hipSuccess && ran[4] == 1);
+  }
+  for (int& r : ran) r = 0;
+  {  // the third fails: the first two ran once, the fourth not at all, and the error stays
+    Deferred d(st);
+    (void)note(0, hipSuccess);
+    (void)note(1, hipSuccess);
+    (void)note(2, hipErrorLaunchFailure);
+    (void)note(3, hipSuccess);  // its status left unread
+    CHECK(note(4, hipSuccess) == hipErrorLaunchFailure);
+    CHECK(st.issue() == hipErrorLaunchFailure && d.done() == hipErrorLaunchFailure);
+    CHECK(ran[0] == 1 && ran[1] == 1 && ran[2] == 1 && ran[3] == 0 && ran[4] == 0);
+  }
+  for (int& r : ran) r = 0;
+  {  // a call that ends early: what it noted is dropped
+    Deferred d(st);
+    (void)note(0, hipSuccess);
+  }
+  CHECK(ran[0] == 0 && !st.deferred && note(1, hipSuccess) == hipSuccess && ran[1] == 1);
+  {  // ... and the next one starts afresh
+    Deferred d(st);
+    CHECK(note(2, hipSuccess) == hipSuccess && d.done() == hipSuccess && ran[2] == 1 && ran[0] == 0);
+  }
+  return 0;
+}
+"""
+
+
+def test_noted_launches_run_once(tmp_path):
+    """Launches that wait for their tables' copy: in order and once each, none
+    after one that failed, none left over from a call that ended early, and a
+    failure is reported by every later status of the call."""
+    lib = os.path.dirname(P.LIB_PATH)
+    _run(tmp_path, STAGING, (build._hipcc(), *build.COMMON), ("-L", lib, "-lhss", f"-Wl,-rpath,{lib}"))
