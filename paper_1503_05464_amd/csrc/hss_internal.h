@@ -219,6 +219,8 @@ struct GemmDesc {
 hipError_t launch_gemm_batched(const GemmDesc* descs, int nprob, Staging& st, hipStream_t s,
                                int variant = -1);
 int gemm_variants();
+// Compute units of the first device this process used (256 on MI355X).
+int compute_units();
 
 // ---------------------------------------------------------------------------
 // Batched interpolative decomposition (kernels_qrcp.hip)

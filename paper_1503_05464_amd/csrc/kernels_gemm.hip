@@ -333,8 +333,7 @@ static int gemm_class(const GemmDesc* descs, int nprob) {
   return nb * 3 + mb;
 }
 
-// Compute units of the current device (256 on MI355X).
-static int compute_units() {
+int compute_units() {
   static const int v = [] {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

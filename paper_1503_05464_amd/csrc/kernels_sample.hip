@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "hss_internal.h"
+#include "sample_plan.h"
 
 namespace hss {
 namespace {
@@ -333,8 +334,9 @@ Plan make_plan(long long n, int ncols, int bk) {
   p.n_mt = (int)((n + BM - 1) / BM);
   p.n_nt = (ncols + BN - 1) / BN;
   const long long tiles = (long long)p.n_mt * p.n_nt;
-  const long long want = (1024 + tiles - 1) / tiles;  // 4 workgroups per CU (the resident maximum)
-  const long long small = n >= kSmallN ? std::min({16LL, n / 64, 512 / tiles}) : 1;
+  const int cus = compute_units();
+  const long long want = (4LL * cus + tiles - 1) / tiles;  // 4 workgroups per CU (the resident maximum)
+  const long long small = small_splits(n, tiles, kSmallN, 64, cus);
   const long long splits = std::max(1LL, std::min(want, std::max(n / 1024, small)));
   long long chunk = (n + splits - 1) / splits;
   chunk = (chunk + bk - 1) / bk * bk;

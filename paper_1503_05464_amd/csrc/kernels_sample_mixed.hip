@@ -39,6 +39,7 @@
 #include <vector>
 
 #include "hss_internal.h"
+#include "sample_plan.h"
 
 namespace hss {
 namespace {
@@ -600,7 +601,7 @@ Plan make_plan(long long n, int ncols) {
   // plain product, us: n = 769 49 / 58 -> 37 / 43, 1500 77 / 93 -> 35 / 42,
   // 3001 83 / 100 -> 39 / 46, 6000 72 / 89 -> 63 / 84; at n = 512 32 -> 35 for
   // BF16x3, hence the line)
-  const long long small = n >= 768 ? std::min({16LL, n / KF, 512 / tiles}) : 1;
+  const long long small = small_splits(n, tiles, 768, KF, compute_units());
   want = std::max(1LL, std::min(want, std::max(n / 1024, small)));
   long long chunk = (n + want - 1) / want;
   chunk = (chunk + KF - 1) / KF * KF;  // split boundaries on carry boundaries

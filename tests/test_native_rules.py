@@ -72,6 +72,34 @@ def test_gemm_offsets_of_a(tmp_path):
     _run(tmp_path, GEMM_OFFSETS)
 
 
+SAMPLE_SPLITS = r"""
+#include <cstdio>
+#include "sample_plan.h"
+using namespace hss;
+int main() {
+  for (int cus : {32, 64, 128, 256, 304})
+    for (long long line : {512, 768})
+      for (long long unit : {64, 256})
+        for (long long n : {100, 511, 512, 767, 768, 1000, 2047, 4096, 8191})
+          for (long long nt : {1, 2, 3, 16}) {
+            const long long tiles = (n + 127) / 128 * nt, s = small_splits(n, tiles, line, unit, cus);
+            const bool ok = n < line ? s == 1 : s <= 16 && s * unit <= n && s * tiles <= 2 * cus;
+            if (!ok) {
+              std::printf("n %lld tiles %lld on %d units: %lld splits\n", n, tiles, cus, s);
+              return 1;
+            }
+          }
+  return small_splits(1024, 8, 512, 64, 256) == 16 && small_splits(6000, 47, 512, 64, 256) == 10 ? 0 : 2;
+}
+"""
+
+
+def test_sample_splits_follow_the_device(tmp_path):
+    """The splits of a small matrix stay within two workgroups per compute
+    unit of the device at hand, not of the largest."""
+    _run(tmp_path, SAMPLE_SPLITS)
+
+
 STAGING = r"""
 #include <cstdio>
 #include "hss_internal.h"
