@@ -109,15 +109,21 @@ __device__ __forceinline__ double buf_load(__amdgpu_buffer_rsrc_t r, unsigned la
 // Held to four wavefronts per SIMD (at most 128 registers), or to three where
 // the LDS of a tile of 128 rows leaves no room for more, or where four blocks
 // per wavefront would spill.
+// SHORT: one slice ahead and no load past the last, for launches whose
+// products have no more than kShortK k.  Their time is that of the outputs,
+// which wants wavefronts: 68 to 128 registers instead of 94 to 168.  Device
+// time, DEEP -> SHORT: 384 products of 300 x 256 with 8 k 184 -> 159 us, 64 of
+// 1000 x 1000 with 16 k 376 -> 302, one of 400 x 700 with 48 k 13.5 -> 13.0.
 // FAR: A is read at 64-bit addresses, for a leading dimension at which 32-bit
 // offsets would wrap (gemm_offsets_fit: from 1048575 on with 512 rows of a
 // transposed A, from 4.2 million on without).
-template <int WGM, int WGN, int MB, int NB, bool FAR = false>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 4 || MB * NB > 2 ? 3 : 4))) void gemm_batched_kernel(
+enum Mode { DEEP, SHORT, FAR };
+template <int WGM, int WGN, int MB, int NB, Mode MODE>
+__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(MODE != SHORT && (WGM * MB > 4 || MB * NB > 2) ? 3 : 4))) void gemm_batched_kernel(
     const DevDesc* __restrict__ descs, const long long* __restrict__ tile0, int nprob) {
   using TL = Tile<WGM, WGN, MB, NB>;
   static_assert(TL::TM <= kGemmMaxRows, "offsets are checked for tiles of at most kGemmMaxRows rows");
-  constexpr int TM = TL::TM, TN = TL::TN, LA = TL::LA, LB = TL::LB, PD = TL::PD;
+  constexpr int TM = TL::TM, TN = TL::TN, LA = TL::LA, LB = TL::LB, PD = MODE == SHORT ? 1 : TL::PD;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   // the problem of this tile: the last whose first tile is not above it; 64
@@ -183,7 +189,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
     ak[q] = tr ? e / TM : e % TK;
     al[q] = ak[q] * (TM + 4) + rr;
     const int rv = min(rr, M - 1 - r0);
-    ao[q] = FAR ? (unsigned)rv : gemm_entry_offset(tr, g.lda, rv, ak[q]);
+    ao[q] = MODE == FAR ? (unsigned)rv : gemm_entry_offset(tr, g.lda, rv, ak[q]);
   }
   const unsigned astep = gemm_slice_step(tr, g.lda);  // from one slice to the next
   const int mt = min(TM, M - r0);  // rows of this tile
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
   auto load = [&](double (&xa)[LA], double (&xb)[LB], int s) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < LA; ++q) {
-      if constexpr (FAR) {
+      if constexpr (MODE == FAR) {
         const long long k = min(s * TK + ak[q], fk), r = ao[q];
         xa[q] = fa[tr ? k * g.lda + r : r * g.lda + k];
       } else {
@@ -231,7 +237,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
       krow[k] = (uintptr_t)seg_row(g.B, g.B.map ? as_global(g.B.map)[kk] : kk);
     }
     const double* a0 = g.A + (tr ? (long long)kc * g.lda + r0 : (long long)r0 * g.lda + kc);
-    if constexpr (FAR) {
+    if constexpr (MODE == FAR) {
       fa = (gdouble_c*)(uintptr_t)a0;
       fk = kn - 1;
     } else {
@@ -261,7 +267,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
           for (int nb = 0; nb < NB; ++nb) b[q][nb] = Bs[u & 1][kr][wn * 16 * NB + nb * 16 + (lane & 15)];
         }
         // past the last slice: the last one again, never stored
-        load(va[u % PD], vb[u % PD], min(s + PD, ns - 1));
+        if (MODE != SHORT || s + PD < ns) load(va[u % PD], vb[u % PD], min(s + PD, ns - 1));
         __builtin_amdgcn_s_setprio(1);  // multiplying wavefronts issue first
 #pragma unroll
         for (int q = 0; q < TK / 4; ++q)
@@ -299,24 +305,30 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(WGM * MB > 
 
 struct GVariant {
   int tm, tn;
-  void (*fn)(const DevDesc*, const long long*, int);
+  void (*fn[2])(const DevDesc*, const long long*, int);  // DEEP, SHORT
 };
+#define GV(A_, B_, C_, D_) {gemm_batched_kernel<A_, B_, C_, D_, DEEP>, gemm_batched_kernel<A_, B_, C_, D_, SHORT>}
 // the tile shapes (index = variant number of the tuning table)
 const GVariant kGVariants[] = {
-    {64, 64, gemm_batched_kernel<2, 2, 2, 2>},
-    {64, 16, gemm_batched_kernel<4, 1, 1, 1>},
-    {128, 16, gemm_batched_kernel<4, 1, 2, 1>},
-    {32, 32, gemm_batched_kernel<2, 2, 1, 1>},
-    {64, 32, gemm_batched_kernel<4, 1, 1, 2>},
-    {128, 32, gemm_batched_kernel<4, 1, 2, 2>},
-    {16, 64, gemm_batched_kernel<1, 4, 1, 1>},
+    {64, 64, GV(2, 2, 2, 2)},
+    {64, 16, GV(4, 1, 1, 1)},
+    {128, 16, GV(4, 1, 2, 1)},
+    {32, 32, GV(2, 2, 1, 1)},
+    {64, 32, GV(4, 1, 1, 2)},
+    {128, 32, GV(4, 1, 2, 2)},
+    {16, 64, GV(1, 4, 1, 1)},
 };
+#undef GV
 // the shape of every launch with an A beyond 32-bit offsets
-const GVariant kGFar = {32, 32, gemm_batched_kernel<2, 2, 1, 1, true>};
+const GVariant kGFar = {32, 32, {gemm_batched_kernel<2, 2, 1, 1, FAR>, gemm_batched_kernel<2, 2, 1, 1, FAR>}};
+// most k of a SHORT launch.  At 48 to 64 k SHORT took 0.82 to 1.0 of DEEP's time
+// in 190 launches of 1 to 384 products of 4 x 20 to 1000 x 1000; above, the
+// two come together (200 k, few tiles: up to 1.1) and the table is DEEP's.
+constexpr int kShortK = 64;
 constexpr int kNumGVariants = sizeof(kGVariants) / sizeof(kGVariants[0]);
 
-#include "gemm_tiles.inc"  // kGemmTileTable[class] = variant (written by autotune.py)
-static_assert(sizeof(kGemmTileTable) / sizeof(kGemmTileTable[0]) == kGemmClasses, "one entry per class");
+#include "gemm_tiles.inc"  // kGemmTileTable[SHORT][class] = variant (written by autotune.py)
+static_assert(sizeof(kGemmTileTable) == 2 * kGemmClasses * sizeof(int), "one entry per class and mode");
 
 }  // namespace
 
@@ -352,10 +364,14 @@ int compute_units() {
 // tile takes more than the device's share of all its tiles goes to such a
 // shape (every shape gives the same bits).  Measured at the top of a matvec
 // with 64 columns (n = 20011, two to four products of about 700 x 64 x 1500):
-// 64 x 64, 28 workgroups, 64 us; 32 x 32, 22 us.
-static int pick_shape(const GemmDesc* descs, int nprob) {
+// 64 x 64, 28 workgroups, 64 us; 32 x 32, 22 us.  Of these shapes 32 x 32 has
+// the most slices in flight (6 against 4 of 16 x 64, which loads five entries
+// a thread and slice for its four): two products of up to 400 rows, 33 to 256
+// columns and 1500 k take 44 to 46 us, 47 to 49 in 16 x 64 and 49 to 51 in
+// 64 x 16.  Where the tiles fill the device, 16 x 64 is the better (the table).
+static int pick_shape(const GemmDesc* descs, int nprob, Mode mode) {
   const int cls = gemm_class(descs, nprob);
-  const int v = kGemmTileTable[cls];
+  const int v = kGemmTileTable[mode == SHORT][cls];
   const int small = cls < 3 ? 1 : 3;  // 64 x 16 up to 16 columns, else 32 x 32
   const GVariant& gv = kGVariants[v];
   long long slices = 0, longest = 0;
@@ -371,18 +387,22 @@ static int pick_shape(const GemmDesc* descs, int nprob) {
 
 hipError_t launch_gemm_batched(const GemmDesc* descs, int nprob, Staging& st, hipStream_t s, int variant) {
   if (nprob <= 0) return hipSuccess;
+  bool far = false;
+  int kmax = 0;
+  for (int p = 0; p < nprob; ++p) {
+    const GemmDesc& g = descs[p];
+    if (g.M <= 0 || g.N <= 0) continue;
+    kmax = std::max(kmax, g.K);
+    far = far || !gemm_offsets_fit(g.transA != 0, g.M, g.K, g.lda);
+  }
+  const Mode mode = far ? FAR : kmax <= kShortK ? SHORT : DEEP;
   if (variant < 0 || variant >= kNumGVariants) {
-    variant = pick_shape(descs, nprob);
+    variant = pick_shape(descs, nprob, mode);
     static const int forced = [] {  // tuning and tests: one variant for every launch
       const char* v = std::getenv("HSS_GEMM_VARIANT");
       return v && v[0] ? std::atoi(v) : -1;
     }();
     if (forced >= 0 && forced < kNumGVariants) variant = forced;
-  }
-  bool far = false;
-  for (int p = 0; p < nprob; ++p) {
-    const GemmDesc& g = descs[p];
-    far = far || (g.M > 0 && g.N > 0 && !gemm_offsets_fit(g.transA != 0, g.M, g.K, g.lda));
   }
   const GVariant& gv = far ? kGFar : kGVariants[variant];
   std::vector<DevDesc> h;
@@ -411,7 +431,7 @@ hipError_t launch_gemm_batched(const GemmDesc* descs, int nprob, Staging& st, hi
   std::memcpy(table.data() + db, tile0.data(), tb);
   char* dd = static_cast<char*>(st.push(table.data(), db + tb));
   if (!dd) return hipErrorOutOfMemory;
-  const auto fn = gv.fn;
+  const auto fn = gv.fn[mode == SHORT];
   const int np = (int)h.size();
   return st.launch([=] {
     hipLaunchKernelGGL(fn, dim3((unsigned)tiles), dim3(NTH), 0, s, reinterpret_cast<const DevDesc*>(dd),

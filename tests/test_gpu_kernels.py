@@ -502,6 +502,29 @@ def test_gemm_batched_long_inner_dimensions(K):
             assert torch.equal(o, f)
 
 
+@pytest.mark.parametrize("K", [0, 1, 16, 17, 33, 64])
+def test_gemm_batched_short_inner_dimensions(K):
+    """Launches of few slices run on kernels with one slice ahead: the same
+    bits in every shape as in a launch that one longer product (200 k) sends
+    to the others, and within 2 gamma_K |A||B| of the host's product."""
+    g = np.random.default_rng(1000 + K)
+    As, Bs, Cs, tr, ref, bnd = [], [], [], [], [], []
+    for M, N, k, t in [(33, 17, K, 0), (70, 65, K, 1), (1, 1, K // 2, 0), (130, 5, K, 1), (16, 64, 200, 0)]:
+        A, B, C = g.standard_normal((k, M) if t else (M, k)), g.standard_normal((k, N)), g.standard_normal((M, N))
+        opA = A.T if t else A
+        ref.append(0.5 * (opA @ B) - C)
+        bnd.append(2 * _gamma(max(k, 1)) * (np.abs(opA) @ np.abs(B)) + 4 * U * (np.abs(opA @ B) + np.abs(C)))
+        for xs, x in zip((As, Bs, Cs), (A, B, C)):
+            xs.append(torch.from_numpy(x).cuda())
+        tr.append(bool(t))
+    print(f"gemm_batched short: K={K}", flush=True)
+    for v in range(-1, P.hss_gemm_variants()):
+        short = P.hss_gemm_batched(As[:4], Bs[:4], [c.clone() for c in Cs[:4]], tr[:4], 0.5, -1.0, v)
+        deep = P.hss_gemm_batched(As, Bs, [c.clone() for c in Cs], tr, 0.5, -1.0, v)
+        for s, d, r, b in zip(short, deep, ref, bnd):
+            assert torch.equal(s, d) and np.all(np.abs(s.cpu().numpy() - r) <= b)
+
+
 @pytest.mark.parametrize("M,N,K,t,lda", [
     (70, 40, 520, 1, 1_048_000),   # offsets reach almost 2^32 bytes
     (70, 40, 520, 1, 1_100_000),   # the last slices of a chunk lie beyond
