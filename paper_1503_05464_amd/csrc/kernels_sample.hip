@@ -23,6 +23,7 @@
 // (deterministic, no atomics).  Consecutive tiles are mapped to the same XCD
 // so that the column tiles sharing an A slice meet in one L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "hss_internal.h"
 #include "sample_plan.h"
@@ -37,7 +38,7 @@ typedef u32x4 u32x4_a4 __attribute__((aligned(4)));  // 16 bytes from any entry 
 constexpr int BM = 128;
 constexpr int BN = 64;
 constexpr int NT = 256;
-constexpr int kSmallN = 512;  // below: K whole in one workgroup, loads for latency (SMALL)
+constexpr int kSmallN = 512;  // below: K whole in one workgroup
 
 template <typename TA>
 struct Cfg;
@@ -57,24 +58,17 @@ __device__ __forceinline__ double widen(TA v) {
   return (double)v;
 }
 
-// This thread's share of the A slice: 4 pieces of 16 bytes, piece q holding
-// the entries (row, col ..) of the slice.  FP64, NN (A[i][k]): row tid / 8 +
-// 32 q, so that eight consecutive lanes read one row's 128 bytes in one
-// instruction.  FP32, NN: 64 bytes of one row (with eight lanes per row the
-// stores to LDS collide: 2.9 against 2.05 ms at n = 32768).  TN (A[k][i]): 64
-// bytes of row kk.  The loads need only the alignment of an entry, and go
-// through the caches (streamed past them, the four loads of a lane's 64
-// bytes fetched their lines more than once).  64 columns, ms, before ->
-// now: FP64 n = 20011 NN 1.78 -> 1.24, TN 1.18 -> 1.09; n = 32768 NN 2.71 ->
-// 2.45, TN 2.55 -> 2.34; FP32 n = 20011 NN 1.56 -> 1.05, TN 1.16 -> 1.05;
-// n = 32768 NN 2.13 -> 2.04, TN 2.10 -> 2.05.
-// SMALL (n < kSmallN): a few workgroups wait for every slice, so what counts
-// is its latency.  64 bytes of one row in FP64 too (eight lanes to a row
-// collide in the stores to LDS), and a thread of an edge tile whose own bytes
-// are there does not share the other threads' scalar loads.  Both products,
-// us, SMALL against the other form: FP64 n = 100 28.8 / 31.9, 256 52.5 / 57.5,
-// 511 109 / 122; FP32 100 30 / 32.5, 511 99 / 124.
-template <typename TA, bool TRANS, bool SMALL>
+// This thread's share of the A slice: 64 bytes of one row (NN: of A[i][k], TN:
+// of A[k][i]) in 4 pieces of 16, piece q holding the entries (row, col ..) of
+// the slice.  (Eight consecutive lanes to a row, FP64 NN: the stores to LDS
+// collide, 10.2 against 9.7 ms at n = 65536, 4.9 against 4.0 at 40960.)  The
+// loads need only the alignment of an entry, and go through the caches
+// (streamed past them, the four loads of a thread fetch their lines more than
+// once).  64 columns, ms, four scalar loads where rows are off the 16-byte
+// grid, streamed elsewhere -> now: FP64 n = 20011 NN 1.78 -> 1.10, TN 1.15 ->
+// 1.03; n = 32768 NN 2.67 -> 2.36, TN 2.52 -> 2.39; FP32 n = 20011 NN 1.56 -> 0.97,
+// TN 1.15 -> 0.97; n = 32768 NN 2.09 -> 2.02, TN 2.10 -> 2.05.
+template <typename TA, bool TRANS>
 __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
   constexpr int E = 64 / sizeof(TA), EV = 16 / sizeof(TA);
   constexpr int BK = Cfg<TA>::BK;
@@ -82,16 +76,21 @@ __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
   if (TRANS) {
     row = tid / (BM / E);
     col = (tid % (BM / E)) * E + q * EV;
-  } else if (sizeof(TA) == 8 && !SMALL) {
-    row = (tid >> 3) + 32 * q;
-    col = (tid & 7) * EV;
   } else {
     row = tid / (BK / E);
     col = (tid % (BK / E)) * E + q * EV;
   }
 }
 
-template <typename TA, bool TRANS, bool SMALL>
+// OWN: a thread takes wide loads where its own 64 bytes are inside; otherwise
+// where the whole slice is.  OWN serves the tiles at the edge of the matrix
+// (scalar loads for all of such a tile held the launch up: n = 8191, FP64,
+// one column 435 -> 350 us a product), and, throughout, two kinds of launches:
+// n < kSmallN, where a few workgroups wait for every slice (FP64 n = 256, both
+// products, 57 -> 52 us), and the transposed product of few columns, whose loads
+// of R have branches of their own (FP32 n = 40000, one column 3.87 -> 3.36 ms;
+// 64 columns, without them, 3.36 -> 3.33, but 8.06 -> 8.20 at n = 65536).
+template <typename TA, bool TRANS, bool OWN>
 __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __restrict__ A,
                                        long long lda, int n, int i0, int k0, int kend,
                                        const int* __restrict__ leaf_of, bool need_mask) {
@@ -99,14 +98,14 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
   const int rbeg = !TRANS ? i0 : k0, cbeg = !TRANS ? k0 : i0;
   const auto mine = [&] {  // this thread's 64 bytes of the slice are there
     int row, col;
-    a_piece<TA, TRANS, true>(0, row, col);
+    a_piece<TA, TRANS>(0, row, col);
     return rbeg + row < (!TRANS ? n : kend) && cbeg + col + 4 * EV <= (!TRANS ? kend : n);
   };
-  if (SMALL ? mine() : i0 + BM <= n && k0 + Cfg<TA>::BK <= kend) {  // or the whole slice is
+  if (OWN ? mine() : i0 + BM <= n && k0 + Cfg<TA>::BK <= kend) {  // or the whole slice is
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int row, col;
-      a_piece<TA, TRANS, SMALL>(q, row, col);
+      a_piece<TA, TRANS>(q, row, col);
       const u32x4_a4* p = reinterpret_cast<const u32x4_a4*>(A + (long long)(rbeg + row) * lda + cbeg + col);
       u32x4 w = *p;
       TA* t = reinterpret_cast<TA*>(&w);
@@ -118,7 +117,7 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int row, col;
-      a_piece<TA, TRANS, SMALL>(q, row, col);
+      a_piece<TA, TRANS>(q, row, col);
 #pragma unroll
       for (int e = 0; e < EV; ++e)
         v[q * EV + e] = (rbeg + row < rend && cbeg + col + e < cend)
@@ -131,7 +130,7 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       int row, col;
-      a_piece<TA, TRANS, SMALL>(q, row, col);
+      a_piece<TA, TRANS>(q, row, col);
 #pragma unroll
       for (int e = 0; e < EV; ++e)
         if (rbeg + row < n && cbeg + col + e < n && leaf_of[rbeg + row] == leaf_of[cbeg + col + e])
@@ -140,13 +139,13 @@ __device__ __forceinline__ void load_a(TA (&v)[64 / sizeof(TA)], const TA* __res
   }
 }
 
-template <typename TA, bool TRANS, bool SMALL>
+template <typename TA, bool TRANS>
 __device__ __forceinline__ void store_a(TA (*As)[BM + Cfg<TA>::PAD], const TA (&v)[64 / sizeof(TA)]) {
   constexpr int EV = 16 / sizeof(TA);
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     int row, col;
-    a_piece<TA, TRANS, SMALL>(q, row, col);
+    a_piece<TA, TRANS>(q, row, col);
 #pragma unroll
     for (int e = 0; e < EV; ++e) {
       if (TRANS) As[row][col + e] = v[q * EV + e];
@@ -190,7 +189,7 @@ __device__ __forceinline__ void store_r(double (*Bs)[BN + 4], const double (&v)[
   for (int e = 0; e < ER; ++e) Bs[rr][cc + e] = v[e];
 }
 
-template <typename TA, bool TRANS, bool SMALL>
+template <typename TA, bool TRANS, bool OWN>
 __global__ __launch_bounds__(NT) void sample_kernel(
     const TA* __restrict__ A, long long lda, int n, const int* __restrict__ leaf_of,
     const double* __restrict__ R, long long ldr, double* __restrict__ S, long long lds, int ncols,
@@ -235,55 +234,59 @@ __global__ __launch_bounds__(NT) void sample_kernel(
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc[a][b] = dbl4{0.0, 0.0, 0.0, 0.0};
 
-  TA va[E];
-  double vr[BK / 4];
-  auto mask_for = [&](int k0) -> bool {
-    if (!leaf_of || k0 >= kend) return false;
-    const int lk0 = leaf_of[k0];
-    const int lk1 = leaf_of[min(k0 + BK, kend) - 1];
-    return !(lk1 < li0 || li1 < lk0);
-  };
+  const auto products = [&](auto own) __attribute__((always_inline)) {
+    TA va[E];
+    double vr[BK / 4];
+    auto mask_for = [&](int k0) -> bool {
+      if (!leaf_of || k0 >= kend) return false;
+      const int lk0 = leaf_of[k0];
+      const int lk1 = leaf_of[min(k0 + BK, kend) - 1];
+      return !(lk1 < li0 || li1 < lk0);
+    };
 
-  int k0 = kbeg;
-  if (k0 < kend) {
-    load_a<TA, TRANS, SMALL>(va, A, lda, n, i0, k0, kend, leaf_of, mask_for(k0));
-    load_r<BK>(vr, R, ldr, k0, kend, c0, ncols, vec_r);
-    store_a<TA, TRANS, SMALL>(As, va);
-    store_r<BK>(Bs, vr);
-  }
-  __syncthreads();
-  for (; k0 < kend; k0 += BK) {
-    const int kn = k0 + BK;
-    if (kn < kend) {
-      load_a<TA, TRANS, SMALL>(va, A, lda, n, i0, kn, kend, leaf_of, mask_for(kn));
-      load_r<BK>(vr, R, ldr, kn, kend, c0, ncols, vec_r);
-    }
-    // the wavefronts multiplying take issue priority over those still
-    // loading or storing the next slice (8.99 -> 8.36 ms per launch at
-    // n = 65536, 64 columns)
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      const int kr = kk + (lane >> 4);
-      double a[4], b[2];
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb) a[mb] = widen(As[kr][wm * 64 + mb * 16 + (lane & 15)]);
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) b[nb] = Bs[kr][wn * 32 + nb * 16 + (lane & 15)];
-#pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-          acc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mb], b[nb], acc[mb][nb], 0, 0, 0);
-    }
-    __builtin_amdgcn_s_setprio(0);
-    __syncthreads();
-    if (kn < kend) {
-      store_a<TA, TRANS, SMALL>(As, va);
+    int k0 = kbeg;
+    if (k0 < kend) {
+      load_a<TA, TRANS, own.value>(va, A, lda, n, i0, k0, kend, leaf_of, mask_for(k0));
+      load_r<BK>(vr, R, ldr, k0, kend, c0, ncols, vec_r);
+      store_a<TA, TRANS>(As, va);
       store_r<BK>(Bs, vr);
     }
     __syncthreads();
-  }
+    for (; k0 < kend; k0 += BK) {
+      const int kn = k0 + BK;
+      if (kn < kend) {
+        load_a<TA, TRANS, own.value>(va, A, lda, n, i0, kn, kend, leaf_of, mask_for(kn));
+        load_r<BK>(vr, R, ldr, kn, kend, c0, ncols, vec_r);
+      }
+      // the wavefronts multiplying take issue priority over those still
+      // loading or storing the next slice (8.99 -> 8.36 ms per launch at
+      // n = 65536, 64 columns)
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 4) {
+        const int kr = kk + (lane >> 4);
+        double a[4], b[2];
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb) a[mb] = widen(As[kr][wm * 64 + mb * 16 + (lane & 15)]);
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) b[nb] = Bs[kr][wn * 32 + nb * 16 + (lane & 15)];
+#pragma unroll
+        for (int mb = 0; mb < 4; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb)
+            acc[mb][nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mb], b[nb], acc[mb][nb], 0, 0, 0);
+      }
+      __builtin_amdgcn_s_setprio(0);
+      __syncthreads();
+      if (kn < kend) {
+        store_a<TA, TRANS>(As, va);
+        store_r<BK>(Bs, vr);
+      }
+      __syncthreads();
+    }
+  };
+  if (OWN || i0 + BM > n) products(std::true_type{});
+  else products(std::false_type{});
 
   // D layout of the 16x16x4 f64 MFMA on gfx950 (checked on the device):
   // lane l, register r -> row l/16 + 4r, column l%16.
@@ -350,7 +353,8 @@ void run(const TA* A, long long lda, long long n, const int* leaf_of, int ncols,
          long long ldr, double* S, long long lds, double* work, hipStream_t s) {
   Plan p = make_plan(n, ncols, Cfg<TA>::BK);
   const long long nblocks = (long long)p.n_mt * p.n_nt * p.ksplit;
-  const auto fn = n < kSmallN ? sample_kernel<TA, TRANS, true> : sample_kernel<TA, TRANS, false>;
+  const bool own = n < kSmallN || (TRANS && ncols < BN);  // see load_a
+  const auto fn = own ? sample_kernel<TA, TRANS, true> : sample_kernel<TA, TRANS, false>;
   hipLaunchKernelGGL(fn, dim3((unsigned)nblocks), dim3(NT), 0, s, A, lda, (int)n, leaf_of, R, ldr, S, lds, ncols,
                      p.n_nt, p.ksplit, p.kchunk, work);
   if (p.ksplit > 1) {
