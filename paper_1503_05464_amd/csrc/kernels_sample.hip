@@ -61,13 +61,13 @@ __device__ __forceinline__ double widen(TA v) {
 // This thread's share of the A slice: 64 bytes of one row (NN: of A[i][k], TN:
 // of A[k][i]) in 4 pieces of 16, piece q holding the entries (row, col ..) of
 // the slice.  (Eight consecutive lanes to a row, FP64 NN: the stores to LDS
-// collide, 10.2 against 9.7 ms at n = 65536, 4.9 against 4.0 at 40960.)  The
+// collide, 10.2 against 9.7 ms at n = 65536, 4.9 against 4.0 at 40000.)  The
 // loads need only the alignment of an entry, and go through the caches
 // (streamed past them, the four loads of a thread fetch their lines more than
 // once).  64 columns, ms, four scalar loads where rows are off the 16-byte
-// grid, streamed elsewhere -> now: FP64 n = 20011 NN 1.78 -> 1.10, TN 1.15 ->
-// 1.03; n = 32768 NN 2.67 -> 2.36, TN 2.52 -> 2.39; FP32 n = 20011 NN 1.56 -> 0.97,
-// TN 1.15 -> 0.97; n = 32768 NN 2.09 -> 2.02, TN 2.10 -> 2.05.
+// grid, streamed elsewhere -> now: FP64 n = 20011 NN 1.78 -> 1.09, TN 1.15 ->
+// 1.04; n = 32768 NN 2.67 -> 2.37, TN 2.52 -> 2.40; FP32 n = 20011 NN 1.56 -> 0.97,
+// TN 1.15 -> 0.97; n = 32768 NN 2.09 -> 2.01, TN 2.10 -> 2.03.
 template <typename TA, bool TRANS>
 __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
   constexpr int E = 64 / sizeof(TA), EV = 16 / sizeof(TA);
@@ -85,7 +85,7 @@ __device__ __forceinline__ void a_piece(int q, int& row, int& col) {
 // OWN: a thread takes wide loads where its own 64 bytes are inside; otherwise
 // where the whole slice is.  OWN serves the tiles at the edge of the matrix
 // (scalar loads for all of such a tile held the launch up: n = 8191, FP64,
-// one column 435 -> 350 us a product), and, throughout, two kinds of launches:
+// one column, both products 435 -> 350 us), and, throughout, two kinds of launches:
 // n < kSmallN, where a few workgroups wait for every slice (FP64 n = 256, both
 // products, 57 -> 52 us), and the transposed product of few columns, whose loads
 // of R have branches of their own (FP32 n = 40000, one column 3.87 -> 3.36 ms;
