@@ -10,6 +10,7 @@ Tolerances (FP64, u = 2^-53):
   equal exactly; E = (R1^{-1} R2)^T agrees to 1e-10 relative (the QR
   factors differ by rounding, amplified by cond(R1)).
 """
+import os
 import re
 
 import numpy as np
@@ -429,6 +430,43 @@ def test_persistent_widths_agree(d, widest, monkeypatch, capfd):
     X[:, perm[k:]] = E.T
     res = np.linalg.norm(y - y[:, perm[:k]] @ X, 2)
     assert res <= 10 * np.sqrt(max(1, m - k)) * rtol * np.linalg.norm(y, axis=0).max()
+
+
+def _persistent_widths():
+    """{rows per lane: columns per wavefront} of the persistent instantiations."""
+    path = os.path.join(os.path.dirname(P.__file__), "csrc", "kernels_qrcp.hip")
+    widths = {}
+    for t, c in re.findall(r"PV\((\d+), (\d+)\)", open(path).read()):
+        widths.setdefault(int(t), []).append(int(c))
+    return widths
+
+
+@pytest.mark.parametrize("T", [4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40])
+def test_persistent_widths_all_run(T, monkeypatch, capfd):
+    """Each instantiation of the persistent kernel, by the workgroups that its
+    launch reports: a cap of ceil(m / (8 C)) rules out narrower columns than C,
+    and wider ones cost more by the model.  m is such that no two widths take
+    the same number.  All give the same ID."""
+    widths = _persistent_widths()
+    assert sorted(widths) == [4, 6, 8, 12, 16, 20, 24, 28, 32, 36, 40]
+    m = 300 if T == 4 else 280
+    d = 64 * T - 20
+    want = [-(-m // (8 * c)) for c in widths[T]]
+    assert len(set(want)) == len(want)
+    Y = torch.from_numpy(np.ascontiguousarray(_slow_decay(d, m, d, 0.1).T)).cuda()
+    monkeypatch.setenv("HSS_QRCP_PATH", "persistent")
+    monkeypatch.setenv("HSS_VERBOSE", "2")
+    first, seen = None, []
+    for cap in want:
+        monkeypatch.setenv("HSS_QRCP_PERSIST_WG", str(cap))
+        capfd.readouterr()
+        k, perm, E = P.hss_id_batched([Y], 1e-6)[0]
+        err = capfd.readouterr().err
+        assert "persistent wait gave up" not in err
+        seen += [int(g) for g in re.findall(r"persistent launch: 1 problems, (\d+) workgroups", err)]
+        first = first or (k, perm, E)
+        assert k == first[0] and np.array_equal(perm, first[1]) and np.array_equal(E, first[2])
+    assert seen == want
 
 
 @pytest.mark.parametrize("variant", list(range(-1, 7)))
