@@ -1211,7 +1211,8 @@ __global__ __launch_bounds__(PT) void qrcp_persist_kernel(const DevProb* __restr
     // workgroup-major records: the G records of one step lie in G different
     // cache lines (and memory channels), not packed into a few lines that
     // every poller of the problem would hit (2.5 us from the last record to
-    // its readers with packed records, against a 0.5 us one-way latency)
+    // its readers with packed records, against 0.45 one way inside an XCD
+    // and 0.58 across)
     const unsigned long long* recs = w.rec + 2 * ((long long)dp.g0 * w.rstride + i);
     const long long rs2 = 2 * w.rstride;
     const unsigned long long want = (unsigned long long)(i + 1);
@@ -1532,7 +1533,7 @@ __device__ __forceinline__ bool trsm_diag_solve(double (&x)[TC], const double (*
 // search for the descriptor, rows of R1 loaded four at a time behind their
 // permutation entries, and x strided by k across lanes; here the loop is
 // short, every row of R1 and of E is one contiguous load, all in flight.
-// 64-row blocks take 13 us per launch.
+// 64-row blocks take 13 to 14 us per launch.
 __global__ __launch_bounds__(TW * 64) void trsm_diag_kernel(const DiagDesc* __restrict__ descs) {
   __shared__ double Rt[64][64];
   const DiagDesc g = descs[blockIdx.x];
@@ -1618,7 +1619,8 @@ static int small_class(const IdProblem& p) {
 // architectural registers (up to 96 values per lane; one step wider, 8 x 12,
 // 12 x 8 or 20 x 5, spills or moves through accumulation registers and takes
 // 1.3 to 1.8 times as long per step).  36 x 3 spills a few and still is the
-// better: half the launches of 36 x 2 for problems of 2700 columns.
+// better: half the launches of 36 x 2 for problems of 2700 columns, at 7.2 to
+// 7.9 us a step against 6.3 to 6.4.
 struct PVariant {
   int T, C;
   const void* fn;
@@ -1643,10 +1645,13 @@ constexpr int kNumPVariants = sizeof(kPVariants) / sizeof(kPVariants[0]);
 // cost model constants (measured on gfx950): time per pivot step of a
 // persistent launch, a base and terms that grow with the values per lane
 // (T C) and with the workgroups of its widest problem, each of which
-// publishes a candidate every step (3.7 us at 32 values and 10 workgroups,
-// 4.3 at 64 and 5, 5.4 at 96 and 28, 7.0 at 96 and 116), and per launch; the
-// floor of one step-path launch, and the rate at which the step path moves
-// the active rows
+// publishes a candidate every step, and per launch; the floor of one
+// step-path launch, and the rate at which the step path moves the active
+// rows.  Model over measured, 79 points over every width above (3 to 75
+// workgroups): median 0.97; 0.87 to 1.10 up to
+// T = 24, 0.82 to 0.98 at 28, 0.79 to 0.92 at 32, 0.69 to 0.86 at 36 and 0.69
+// to 0.78 at 40.  Low where columns are long, but alike for the widths of one
+// T, between which it chooses.
 constexpr double kPersistLaunchUs = 20.0;
 constexpr double kPersistStepUs = 2.8;
 constexpr double kPersistStepUsPerValue = 0.022;

@@ -130,8 +130,8 @@ __device__ __forceinline__ double lane_bcast(double v, int l) {
 // What bounds it: that chain of steps.  Every lane divides its own x by its
 // own diagonal entry each step, by a reciprocal taken once, and the entries
 // of T come from LDS ahead of the chain (eight steps unrolled), staged with
-// every load in flight: 17.5 -> 7.6 us
-// per launch of 64-row blocks, against a division and two LDS latencies in
+// every load in flight: 17.5 -> 6.9 us
+// per launch of 64-row blocks (n = 12007, 33 columns), against a division and two LDS latencies in
 // every step.  A diagonal outside 2^+-500, or a quotient that quot_by may
 // round otherwise, takes the plain division: the whole block again.
 template <bool LOWER, bool PLAIN>
